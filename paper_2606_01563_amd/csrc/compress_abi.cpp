@@ -84,8 +84,10 @@ mkv::CompressArgs compress_layout(const mkv_compress_params* p, void* ws, size_t
   a.nsl1 = clampi(ceil_div(256, a.H), 1, a.ntile);
   a.tps1 = std::min(ceil_div(a.ntile, a.nsl1), mkv::kRowsMaxTiles);
   a.nsl1 = ceil_div(a.ntile, a.tps1);
-  // window-mass pass: about 1024 workgroups of 256 threads
-  a.nsl2 = clampi(ceil_div(1024, a.H), 1, a.ntile);
+  // window-mass pass: about 512 workgroups of 256 threads, two per CU, so that all of them
+  // run at once (each start costs the queries and the first keys: about 4 us; 128K context,
+  // 1024 workgroups 100 us, 512 workgroups 89)
+  a.nsl2 = clampi(ceil_div(512, a.H), 1, a.ntile);
   a.tps2 = std::min(ceil_div(a.ntile, a.nsl2), mkv::kMassMaxTiles);
   a.nsl2 = ceil_div(a.ntile, a.tps2);
   // top-k slices of 2048 candidates (at most 512 for kMaxCandidates); each slice's

@@ -10,7 +10,7 @@ namespace mkv {
 // Most 64-token tiles one workgroup of the window-row/covariance, window-mass and
 // residual passes takes: its per-token results wait in LDS until its tile loop ends.
 constexpr int kRowsMaxTiles = 64;
-constexpr int kMassMaxTiles = 8;
+constexpr int kMassMaxTiles = 32;
 constexpr int kResMaxTiles = 32;
 
 struct CompressArgs {

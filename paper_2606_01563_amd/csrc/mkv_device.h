@@ -157,16 +157,23 @@ __device__ __forceinline__ float quad_sum(float x) {
   x += dpp_f<0x4E>(x);  // quad_perm [2,3,0,1]
   return x;
 }
-// Sum over lanes l, l^16, l^32, l^48 (the four 16-lane rows), same value in each.
+// Sum over lanes l, l^16, l^32, l^48 (the four 16-lane rows), same value in each.  The row
+// and half swaps of gfx950 are vector instructions (a shuffle is an LDS round trip): of two
+// copies of x, one ends with rows (0, 0, 2, 2), the other with rows (1, 1, 3, 3); the
+// halves likewise.
+template <class F>
+__device__ __forceinline__ float cross_row(float x, F f) {
+  const uint32_t u = __float_as_uint(x);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const uint32_t y = __float_as_uint(f(__uint_as_float(r[0]), __uint_as_float(r[1])));
+  const auto h = __builtin_amdgcn_permlane32_swap(y, y, false, false);
+  return f(__uint_as_float(h[0]), __uint_as_float(h[1]));
+}
 __device__ __forceinline__ float cross_row_sum(float x) {
-  x += __shfl_xor(x, 16);
-  x += __shfl_xor(x, 32);
-  return x;
+  return cross_row(x, [](float p, float q) { return p + q; });
 }
 __device__ __forceinline__ float cross_row_max(float x) {
-  x = fmaxf(x, __shfl_xor(x, 16));
-  x = fmaxf(x, __shfl_xor(x, 32));
-  return x;
+  return cross_row(x, [](float p, float q) { return fmaxf(p, q); });
 }
 __device__ __forceinline__ float wave_sum(float x) { return cross_row_sum(row16_sum(x)); }
 __device__ __forceinline__ float wave_max(float x) { return cross_row_max(row16_max(x)); }

@@ -231,6 +231,18 @@ def test_window_rows_not_a_multiple_of_16(q_scale):
         P.check_compress_head(cpu, out, 0, h, 60)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Hq,w", [(1, 16), (4, 16), (5, 13), (4, 32), (3, 43), (16, 16), (16, 32)])
+def test_window_row_tiles_of_the_mass_pass(Hq, w, d):
+    """Window rows on both sides of the row-tile splits (16, 64, 65, 128, 129, 256 and 512
+    rows), over a ragged context of one and a bit slices' last tiles."""
+    ctx, L = 1177, 97
+    wl, cpu, gpu = layer("tiny_fp32_n2048", steps=1, dtype=torch.bfloat16, head_dim=d, ctx_len=ctx,
+                         n_q_heads=Hq, n_kv_heads=1, window=w, budgets=(L,))
+    out = P.run_compress(gpu, L, cap=L)
+    announce(f"rows {Hq * w} d {d}: {P.check_compress_head(cpu, out, 0, 0, L)}")
+
+
 @pytest.mark.parametrize("mi_rounds", [-1, 0, 1])
 @pytest.mark.parametrize("chunk", [1, 4, 8])
 def test_selection_modes_and_chunks(mi_rounds, chunk):
