@@ -39,6 +39,8 @@
 //                     idx, lens; and the final raw moments S, s_k, s_v, n_e (the slots of
 //                     the final selection's covariance, as in stage 7).
 // Every reduction has a fixed order, so results are bit-reproducible.
+#include <climits>
+
 #include "mkv_bf16.h"
 #include "mkv_device.h"
 #include "mkv_compress.h"
@@ -48,20 +50,29 @@ namespace mkv {
 constexpr int TILE = 64;  // tokens per tile
 
 // Top-k selection (lowest score evicted first): scores as monotone 32-bit keys, a
-// per-head histogram of key bits 30..20 filled by the kernel that produces the scores,
-// then slices of TKS positions.
+// per-head histogram of the keys filled by the kernel that produces the scores, then
+// slices of TKS positions.
 constexpr int TKS = 2048;          // positions per slice
 constexpr int TKT = 256;           // threads per slice workgroup
 constexpr int TKPT = TKS / TKT;    // consecutive positions per thread
 constexpr int TK_MAX_SLICES = 512; // 1048576 candidates
-constexpr int TK_CAND_LDS = 8192;  // candidates of the k-th key's bin staged in LDS
+constexpr int TK_CAND_LDS = 2048;  // candidates of the k-th key's bin staged in LDS
 
 __device__ __forceinline__ uint32_t score_key(float s) {
   uint32_t u = __float_as_uint(s);
   return (u & 0x80000000u) ? 0u : u;  // -0 and negatives sort as 0
 }
 
-constexpr int TK_HBINS = 2048;     // bins of the per-head histogram (key bits 30..20)
+// Bins of the per-head histogram: 64 per octave from 2^-28 to 2^4, where the k-th score of
+// a mass that sums to at most one falls for values of any usual scale (keys outside land in
+// the end bins: the selection stays exact, over more candidates).  Eight bins per octave
+// over all exponents left eight times the candidates at the threshold.
+constexpr int TK_HBINS = 2048;
+constexpr int TK_SHIFT = 17;
+constexpr int TK_BASE = (127 - 28) << (23 - TK_SHIFT);
+__device__ __forceinline__ int key_bin(uint32_t key) {
+  return min(max((int)(key >> TK_SHIFT) - TK_BASE, 0), TK_HBINS - 1);
+}
 
 // Candidates kept by a head: the uniform k_keep, or its head-adaptive share (clamped to
 // the buffers, since it sizes reads and writes).
@@ -648,6 +659,13 @@ __global__ void __launch_bounds__(256) k_row_combine(CompressArgs a) {
   if (blockIdx.x == 0) {  // the score producers below add into these
     for (int b = threadIdx.x; b < 2 * TK_HBINS; b += 256)
       a.tk_hh[((size_t)(b / TK_HBINS) * a.H + head) * TK_HBINS + b % TK_HBINS] = 0u;
+    if (threadIdx.x == 0) {
+      a.tk_arr[head] = 0;
+      if (a.adaptive) {
+        a.kh[head] = 0;
+        a.tk_arr_g[head / a.Hkv] = 0;
+      }
+    }
     if (a.adaptive && head % a.Hkv == 0)
       for (int b = threadIdx.x; b < TK_HBINS; b += 256)
         a.tk_hs[(size_t)(head / a.Hkv) * TK_HBINS + b] = 0u;
@@ -706,8 +724,8 @@ __device__ __forceinline__ void mass_scores(const CompressArgs& a, int head, int
         const float s0 = ab * vn[u];
         a.abar[o] = ab;
         a.score0[o] = s0;
-        atomicAdd(&sHist[score_key(a.mi_rounds < 0 ? ab : s0) >> 20], 1u);
-        if (a.adaptive) atomicAdd(&sHistA[score_key(ab) >> 20], 1u);
+        atomicAdd(&sHist[key_bin(score_key(a.mi_rounds < 0 ? ab : s0))], 1u);
+        if (a.adaptive) atomicAdd(&sHistA[key_bin(score_key(ab))], 1u);
       }
     }
   }
@@ -1005,48 +1023,41 @@ __global__ void __launch_bounds__(256, 2) k_mass_stream(CompressArgs a) {
 // Stage 4/9: per-head selection of the k best scores (ties: lower position first),
 // output in ascending position order.  Scores are non-negative floats, so their bit
 // patterns (bit 31 clear) order like unsigned integers ("keys").  The kernel producing
-// the scores (k_mass, k_residual) also adds each key's bits 30..20 into the head's
-// histogram; then two launches over slices of TKS positions spread over all CUs:
+// the scores (k_mass, k_residual) also adds each key's bin into the head's histogram; then
+// two launches over slices of TKS positions spread over all CUs:
 //   k_tk_cand   slices x heads: from the head's histogram, the bin B of the k-th largest
-//               key and the count of keys above B (every slice finds the same); counts the
-//               slice's keys above B and writes its keys inside B (the candidates) in
-//               position order;
-//   k_tk_write  slices x heads: refines bits 19..10 and 9..0 over the head's candidates
-//               (few: one bin spans an eighth of an octave), which gives the k-th key T and
-//               how many keys equal to T are kept (the lowest positions); from the per-slice
-//               counts it gets its slice's output offset and share of equal keys, then
-//               writes the slice's kept positions in order.
+//               key and the count of keys above B (every slice finds the same); hands over
+//               the slice's count of keys above B and its (key, position) pairs inside B
+//               (the candidates: B spans 1/64 of an octave).  The head's last workgroup to
+//               arrive selects among the candidates:
+//               the k-th key T, the last position P kept of the keys equal to T (the lowest
+//               are), and every slice's output offset;
+//   k_tk_write  slices x heads: the slice's kept positions in order (key > T, or = T up to
+//               P), then its covariance slot.
+// Bound by the chain of round trips (the keys and histogram, the hand-over, the count, the
+// last workgroup's reads).  With bins of an eighth of an octave, and the refinement repeated
+// by every slice's workgroup (its LDS left one per CU), the two launches took 21.2 / 23.8 /
+// 53 us for 8 heads of 8K / 32K / 128K; now 18.7 / 19.9 / 29.4.
 // ------------------------------------------------------------------------------------
 // Exclusive scan of one int per thread over an NT-thread block; the total goes to *total.
-// sW holds 2 * NT / 64 + 1 ints.
+// sW holds NT / 64 ints.
 template <int NT>
-__device__ int block_excl_scan(int x, int* sW, int* total) {
+__device__ __forceinline__ int block_excl_scan(int x, int* sW, int* total) {
   constexpr int NW = NT / 64;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int inc = x;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    int y = __shfl_up(inc, o);
-    if (lane >= o) inc += y;
-  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int inc = wave_incl_scan(x);
   if (lane == 63) sW[wave] = inc;
   __syncthreads();
-  if (wave == 0) {
-    int v = lane < NW ? sW[lane] : 0;
-    int vi = v;
+  int before = 0, all = 0;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      int y = __shfl_up(vi, o);
-      if (lane >= o) vi += y;
-    }
-    if (lane < NW) sW[NW + lane] = vi - v;  // exclusive wave offsets
-    if (lane == NW - 1) sW[2 * NW] = vi;
+  for (int w = 0; w < NW; ++w) {
+    const int t = sW[w];
+    before += w < wave ? t : 0;
+    all += t;
   }
-  __syncthreads();
-  const int res = sW[NW + wave] + inc - x;
-  *total = sW[2 * NW];
-  __syncthreads();
-  return res;
+  *total = all;
+  __syncthreads();  // sW may be written again
+  return before + inc - x;
 }
 
 // Over NB histogram bins in descending order, the bin where the running count reaches
@@ -1069,12 +1080,7 @@ __device__ __forceinline__ void wave_find_bin(const uint32_t* hist, int need, ui
   int c = 0;
 #pragma unroll
   for (int q = 0; q < PER; ++q) c += (int)h[q];
-  int inc = c;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(inc, o);
-    if (lane >= o) inc += y;
-  }
+  const int inc = wave_incl_scan(c);
   int before = inc - c;
   uint32_t b = 0u, ab = 0u;
   bool found = false;
@@ -1090,8 +1096,8 @@ __device__ __forceinline__ void wave_find_bin(const uint32_t* hist, int need, ui
   }
   const uint64_t m = __ballot(found);
   const int src = m ? (int)__builtin_ctzll(m) : 0;
-  *bin = (uint32_t)__shfl((int)b, src);
-  *above = (uint32_t)__shfl((int)ab, src);
+  *bin = (uint32_t)__builtin_amdgcn_readlane((int)b, src);
+  *above = (uint32_t)__builtin_amdgcn_readlane((int)ab, src);
 }
 
 // The TKPT consecutive keys of thread tid in slice sl (positions >= n give valid = false).
@@ -1112,15 +1118,196 @@ __device__ __forceinline__ void slice_keys(const float* s, int n, int sl, uint32
   }
 }
 
+// The head's selection by the last workgroup to arrive (see above): the candidates and the
+// per-wave counts are read with agent-scope loads.  Up to TK_CAND_LDS candidates are held
+// in LDS (more only where k or the ties at the threshold run to tens of thousands, or the
+// threshold lies in an end bin: the passes then read them from memory, eight loads in
+// flight per thread).
+struct TkLds {
+  union {
+    __align__(16) uint32_t hist[TK_HBINS];  // the head's histogram,
+    uint64_t cand[TK_CAND_LDS];             // then its candidates
+  };
+  __align__(16) uint32_t digit[2][512];
+  int in_bin[TK_MAX_SLICES];  // candidates kept per slice
+  int start[TK_MAX_SLICES + 1];  // the slices' candidates, flattened
+  uint16_t n_c[64];
+  int W[TKT / 64], last, over;
+};
+
+__device__ __forceinline__ void tk_finish(TkLds& L, int head, int k, int ntk, int B, int above,
+                                          const uint64_t* cnt, const uint64_t* cand, int* sel,
+                                          int* off) {
+  constexpr int U = 8;
+  constexpr int SPT = TK_MAX_SLICES / TKT;  // slices per thread, consecutive
+  constexpr int FC = 32;                    // first candidates of a slice
+  const int tid = threadIdx.x;
+  const uint64_t* ch = cand + (size_t)head * ntk * TKS;
+  // requests: the slices' counts and, where FC of each slice fit in LDS, the first FC
+  // candidates of every slice (a slice seldom has more)
+  uint64_t cn[SPT], first[U];
+#pragma unroll
+  for (int u = 0; u < SPT; ++u) cn[u] = ld_agent_u64(cnt + (size_t)head * ntk + min(SPT * tid + u, ntk - 1));
+  const bool few = ntk <= TK_CAND_LDS / FC;
+  static_assert(TK_CAND_LDS == TKT * U && TK_CAND_LDS / FC <= 64, "one round of requests");
+  if (few) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = min(tid + TKT * u, ntk * FC - 1);
+      first[u] = ld_agent_u64(ch + (size_t)(e / FC) * TKS + e % FC);
+    }
+  }
+  if (tid == 0) L.over = 0;
+  for (int i = tid; i < 2 * 512; i += TKT) L.digit[0][i] = 0;
+  for (int i = tid; i < ntk; i += TKT) L.in_bin[i] = 0;
+  int sum = 0, m, over = 0;
+#pragma unroll
+  for (int u = 0; u < SPT; ++u) {
+    const int c = SPT * tid + u < ntk ? (int)(cn[u] >> 32) : 0;
+    over |= c > FC;
+    sum += c;
+  }
+  int acc = block_excl_scan<TKT>(sum, L.W, &m);
+#pragma unroll
+  for (int u = 0; u < SPT; ++u) {
+    const int i = SPT * tid + u, c = i < ntk ? (int)(cn[u] >> 32) : 0;
+    if (i < ntk) L.start[i] = acc;
+    if (i < 64) L.n_c[i] = (uint16_t)c;
+    acc += c;
+  }
+  if (over) L.over = 1;
+  __syncthreads();
+  // candidate f of the head: its slice by bisection over the slices' starts, then the entry
+  int top = 1;
+  while (2 * top < ntk) top *= 2;  // uniform
+  auto fetch = [&](int f0, uint64_t (&c)[U]) {
+    int s2[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) s2[u] = 0;
+    for (int st = top; st >= 1; st >>= 1)
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int t = min(s2[u] + st, ntk - 1);
+        if (L.start[t] <= min(f0 + TKT * u, m - 1)) s2[u] = t;
+      }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      c[u] = ld_agent_u64(ch + (size_t)s2[u] * TKS + (min(f0 + TKT * u, m - 1) - L.start[s2[u]]));
+  };
+  const bool in_lds = m <= TK_CAND_LDS;
+  if (few && !L.over) {  // uniform; m <= ntk * FC
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = tid + TKT * u, s2 = e / FC;
+      if (s2 < ntk && e % FC < (int)L.n_c[s2]) L.cand[L.start[s2] + e % FC] = first[u];
+    }
+  } else if (in_lds && m > 0) {
+    uint64_t c[U];
+    fetch(tid, c);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (tid + TKT * u < m) L.cand[tid + TKT * u] = c[u];
+  }
+  __syncthreads();
+  auto for_each_cand = [&](auto&& fn) {
+    if (in_lds) {
+      for (int f = tid; f < m; f += TKT) fn(L.cand[f]);
+    } else {
+      for (int f0 = 0; f0 < m; f0 += TKT * U) {
+        uint64_t c[U];
+        fetch(f0 + tid, c);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (f0 + tid + TKT * u < m) fn(c[u]);
+      }
+    }
+  };
+  // The `need`-th largest (on return: the rank among its equals, and their count) of a field
+  // of the candidates that pass a filter, by digits of up to 9 bits below bit `top` (above
+  // it the field is zero).  Two digit histograms, zero on entry, in turn: one is cleared
+  // while the other is filled.
+  int flip = 0;
+  auto select = [&](auto&& field, int top, int& need, int& equal) -> uint32_t {
+    uint32_t prefix = 0u, mask = 0u;
+    for (int hi = top; hi > 0;) {
+      const int shift = max(hi - 9, 0);
+      const uint32_t dm = (1u << (hi - shift)) - 1u;
+      uint32_t* d = L.digit[flip];
+      for_each_cand([&](uint64_t c) {
+        uint32_t x;
+        if (field(c, x) && (x & mask) == prefix) atomicAdd(&d[(x >> shift) & dm], 1u);
+      });
+      __syncthreads();
+      uint32_t b, ab;  // every wave finds the same digit
+      wave_find_bin<512>(d, need, &b, &ab);
+      equal = (int)d[b];
+      prefix |= b << shift;
+      mask |= dm << shift;
+      need -= (int)ab;
+      flip ^= 1;
+      hi = shift;
+      if (hi > 0) {  // the other buffer was read before the last barrier
+        __syncthreads();
+        for (int i = tid; i < 512; i += TKT) L.digit[flip ^ 1][i] = 0;
+      }
+    }
+    return prefix;
+  };
+  // the k-th key: the low bits of a bin inside the range, the whole key in an end bin
+  const bool end_bin = B == 0 || B == TK_HBINS - 1;
+  const uint32_t low = end_bin ? 0u : (uint32_t)(B + TK_BASE) << TK_SHIFT;
+  int need = k - above, equal = 0;
+  const uint32_t T = low + select([&](uint64_t c, uint32_t& x) { x = (uint32_t)(c >> 32) - low; return true; },
+                                  end_bin ? 31 : TK_SHIFT, need, equal);
+  // the last position kept of the keys equal to T: the need-th lowest
+  int P = INT_MAX;
+  if (equal > need) {  // uniform
+    __syncthreads();
+    for (int i = tid; i < 2 * 512; i += TKT) L.digit[0][i] = 0;
+    __syncthreads();
+    constexpr uint32_t PM = (1u << 20) - 1u;  // at most 2^20 positions
+    int nd = need, eq = 0;
+    P = (int)(PM - select([&](uint64_t c, uint32_t& x) { x = PM - (uint32_t)c; return (uint32_t)(c >> 32) == T; }, 20, nd, eq));
+  }
+  for_each_cand([&](uint64_t c) {
+    const uint32_t key = (uint32_t)(c >> 32);
+    const int pos = (int)(uint32_t)c;
+    if (key > T || (key == T && pos <= P)) atomicAdd(&L.in_bin[pos / TKS], 1);
+  });
+  __syncthreads();
+  int kept[SPT], tot;
+  sum = 0;
+#pragma unroll
+  for (int u = 0; u < SPT; ++u) {
+    const int i = SPT * tid + u;
+    kept[u] = 0;
+    if (i < ntk) kept[u] = L.in_bin[i] + (int)(uint32_t)cn[u];
+    sum += kept[u];
+  }
+  int ob = block_excl_scan<TKT>(sum, L.W, &tot);
+#pragma unroll
+  for (int u = 0; u < SPT; ++u) {
+    const int i = SPT * tid + u;
+    if (i < ntk) off[(size_t)head * ntk + i] = ob;
+    ob += kept[u];
+  }
+  if (tid == 0) {
+    sel[2 * head] = (int)T;
+    sel[2 * head + 1] = P;
+  }
+}
+
+// arr: the head's arrival counter (zero between launches); cnt: per slice, the keys above
+// the bin and (high half) in it; cand: the slices' candidates; sel, off: the k-th key and
+// the last position kept of its equals, and per slice its output offset.
 __global__ void __launch_bounds__(TKT) k_tk_cand(const float* __restrict__ scores, int n, int k,
                                                    const int* __restrict__ kh,
                                                    const uint32_t* __restrict__ hh,
-                                                   int* __restrict__ state,
-                                                   int* __restrict__ cnt, uint32_t* __restrict__ cand) {
-  __shared__ int sW[2 * (TKT / 64) + 1];
-  __shared__ __align__(16) uint32_t hst[TK_HBINS];
-  __shared__ uint32_t sh_bin, sh_above;
+                                                   int* arr, uint64_t* cnt,
+                                                   uint64_t* cand, int* sel, int* off) {
+  __shared__ TkLds L;
   const int head = blockIdx.y, sl = blockIdx.x, ntk = gridDim.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (kh) k = min(kh[head], n);  // head-adaptive count (uniform over the workgroup)
   if (k <= 0) return;
   uint32_t key[TKPT];
@@ -1136,38 +1323,50 @@ __global__ void __launch_bounds__(TKT) k_tk_cand(const float* __restrict__ score
 #pragma unroll
     for (int u = 0; u < HPT; ++u) hv[u] = src[threadIdx.x + TKT * u];
 #pragma unroll
-    for (int u = 0; u < HPT; ++u) reinterpret_cast<uint4*>(hst)[threadIdx.x + TKT * u] = hv[u];
+    for (int u = 0; u < HPT; ++u) reinterpret_cast<uint4*>(L.hist)[threadIdx.x + TKT * u] = hv[u];
   }
   __syncthreads();
-  if (threadIdx.x < 64) {
-    uint32_t b, ab;
-    wave_find_bin<TK_HBINS>(hst, k, &b, &ab);
-    if (threadIdx.x == 0) { sh_bin = b; sh_above = ab; }
-  }
-  __syncthreads();
-  const uint32_t B = sh_bin;
-  if (sl == 0 && threadIdx.x == 0) {
-    state[2 * head] = (int)sh_bin;
-    state[2 * head + 1] = (int)sh_above;
-  }
+  uint32_t bin, above;  // every wave finds the same
+  wave_find_bin<TK_HBINS>(L.hist, k, &bin, &above);
+  const int B = (int)bin;
+  // the slice's candidates, counted and placed by ballots (their order does not matter)
   int n_gt = 0, n_c = 0;
+  uint64_t in[TKPT];
 #pragma unroll
   for (int u = 0; u < TKPT; ++u) {
-    n_gt += valid[u] && (key[u] >> 20) > B;
-    n_c += valid[u] && (key[u] >> 20) == B;
+    const int b = key_bin(key[u]);
+    n_gt += __popcll(__ballot(valid[u] && b > B));
+    in[u] = __ballot(valid[u] && b == B);
+    n_c += __popcll(in[u]);
   }
-  // one scan of both counts, packed in 16-bit halves (a slice holds 2048 positions)
-  int tot;
-  const int before = block_excl_scan<TKT>(n_gt | (n_c << 16), sW, &tot);
-  int pos = before >> 16;
-  uint32_t* c = cand + ((size_t)head * ntk + sl) * TKS;
+  if (lane == 0) L.W[wave] = n_gt | (n_c << 16);  // at most 512 of each
+  __syncthreads();
+  int before = 0, tot = 0;
 #pragma unroll
-  for (int u = 0; u < TKPT; ++u)
-    if (valid[u] && (key[u] >> 20) == B) c[pos++] = key[u];
-  if (threadIdx.x == 0) {
-    cnt[((size_t)head * ntk + sl) * 2] = tot & 0xFFFF;
-    cnt[((size_t)head * ntk + sl) * 2 + 1] = tot >> 16;
+  for (int w = 0; w < TKT / 64; ++w) {
+    const int t = L.W[w];
+    before += w < wave ? t >> 16 : 0;
+    tot += t;
   }
+  uint64_t* c = cand + ((size_t)head * ntk + sl) * TKS + before;
+  const int j0 = sl * TKS + TKPT * threadIdx.x;
+#pragma unroll
+  for (int u = 0; u < TKPT; ++u) {
+    if ((in[u] >> lane) & 1)
+      st_agent_u64(c + __popcll(in[u] & ((1ull << lane) - 1ull)), ((uint64_t)key[u] << 32) | (uint32_t)(j0 + u));
+    c += __popcll(in[u]);
+  }
+  if (threadIdx.x == 0)
+    st_agent_u64(cnt + (size_t)head * ntk + sl, (uint64_t)(tot & 0xFFFF) | ((uint64_t)(tot >> 16) << 32));
+  // count in; the last workgroup of the head selects
+  stores_complete();
+  __syncthreads();
+  if (threadIdx.x == 0) L.last = atomicAdd(arr + head, 1) == ntk - 1;
+  __syncthreads();
+  if (!L.last) return;
+  if (threadIdx.x == 0) __hip_atomic_store(arr + head, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  loads_after_count();
+  tk_finish(L, head, k, ntk, B, (int)above, cnt, cand, sel, off);
 }
 
 // COV: the same workgroup then adds the covariance and sums of its slice's kept rows
@@ -1177,175 +1376,84 @@ template <class T, int D>
 __device__ void slice_cov(const CompressArgs& a, int head, int sl, const int32_t* list,
                           int nrows, float sign);
 
-template <class E, int D, bool COV>
+template <class E, int D>
 __global__ void __launch_bounds__(TKT) k_tk_write(const float* __restrict__ scores, int n, int k,
                                                     const int* __restrict__ kh,
-                                                    const int* __restrict__ state,
-                                                    const int* __restrict__ cnt,
-                                                    const uint32_t* __restrict__ cand,
+                                                    const int* __restrict__ sel,
+                                                    const int* __restrict__ off,
                                                     int32_t* __restrict__ out, int out_stride,
                                                     int pos_offset, CompressArgs a) {
-  __shared__ int s_gt[TK_MAX_SLICES], s_cn[TK_MAX_SLICES], s_gtT[TK_MAX_SLICES], s_eqT[TK_MAX_SLICES];
-  __shared__ __align__(16) uint32_t hst[1024];
-  __shared__ uint32_t sh_bin, sh_above;
-  __shared__ int sW[2 * (TKT / 64) + 1];
-  __shared__ int s_off, s_eqb;
-  __shared__ int s_start[TK_MAX_SLICES + 1];
-  __shared__ uint32_t c_key[TK_CAND_LDS];
-  __shared__ uint16_t c_sl[TK_CAND_LDS];
-  __shared__ int32_t s_rows[COV ? TKS : 1];  // the slice's rows for the covariance, in order
-  __shared__ int s_nrows;
+  __shared__ int sW[TKT / 64];
+  __shared__ int32_t s_rows[TKS];  // the slice's rows for the covariance, in order
   const int head = blockIdx.y, sl = blockIdx.x, ntk = gridDim.x, tid = threadIdx.x;
   if (kh) k = min(kh[head], n);  // head-adaptive count (uniform over the workgroup)
   if (k <= 0) {
-    if constexpr (COV) slice_cov<E, D>(a, head, sl, s_rows, 0, -1.f);  // a zero slot
+    slice_cov<E, D>(a, head, sl, s_rows, 0, -1.f);  // a zero slot
     return;
   }
-  // the slice's own keys are needed last but depend on nothing: requested first
   uint32_t key[TKPT];
   bool valid[TKPT];
   slice_keys(scores + (size_t)head * n, n, sl, key, valid);
-  const uint32_t B = (uint32_t)state[2 * head];
-  const int above = state[2 * head + 1];
-  for (int i = tid; i < ntk; i += TKT) {
-    s_gt[i] = cnt[((size_t)head * ntk + i) * 2];
-    s_cn[i] = cnt[((size_t)head * ntk + i) * 2 + 1];
-    s_gtT[i] = 0;
-    s_eqT[i] = 0;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    int acc = 0;
-    for (int i = 0; i < ntk; ++i) { s_start[i] = acc; acc += s_cn[i]; }
-    s_start[ntk] = acc;
-  }
-  __syncthreads();
-  // The head's candidates, flattened in slice order, go to LDS with all loads in flight
-  // (a flat index finds its slice by bisection over the slice starts); past TK_CAND_LDS
-  // candidates the passes read them from global memory instead.
-  const int m = s_start[ntk];
-  const bool in_lds = m <= TK_CAND_LDS;
-  if (in_lds) {
-    // the slice of every flat index first (each slice's range filled in LDS), then all
-    // loads of the thread, from clamped addresses, then the keys' stores
-    for (int s2 = 0; s2 < ntk; ++s2)
-      for (int f = s_start[s2] + tid; f < s_start[s2 + 1]; f += TKT) c_sl[f] = (uint16_t)s2;
-    __syncthreads();
-    constexpr int GU = TK_CAND_LDS / TKT;
-    uint32_t v[GU];
-#pragma unroll
-    for (int u = 0; u < GU; ++u) {
-      if (u * TKT < m) {  // uniform
-        const int f = min(u * TKT + tid, m - 1);
-        const int s2 = c_sl[f];
-        v[u] = cand[((size_t)head * ntk + s2) * TKS + (f - s_start[s2])];
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < GU; ++u) {
-      const int f = u * TKT + tid;
-      if (f < m) c_key[f] = v[u];
-    }
-  }
-  __syncthreads();
-  auto for_each_cand = [&](auto&& fn) {
-    if (in_lds) {
-      for (int f = tid; f < m; f += TKT) fn(c_key[f], (int)c_sl[f]);
-    } else {
-      for (int s2 = 0; s2 < ntk; ++s2) {
-        const uint32_t* c = cand + ((size_t)head * ntk + s2) * TKS;
-        for (int i = tid; i < s_cn[s2]; i += TKT) fn(c[i], s2);
-      }
-    }
-  };
-  // bits 19..10, then 9..0, over the candidates (all of them have bits 30..20 = B)
-  uint32_t prefix = B << 20, mask = 0x7FF00000u;
-  int remaining = k - above;
-  for (int pass = 0; pass < 2; ++pass) {
-    const int shift = pass == 0 ? 10 : 0;
-    for (int i = tid; i < 1024; i += TKT) hst[i] = 0;
-    __syncthreads();
-    for_each_cand([&](uint32_t key, int) {
-      if ((key & mask) == prefix) atomicAdd(&hst[(key >> shift) & 1023u], 1u);
-    });
-    __syncthreads();
-    if (tid < 64) {
-      uint32_t b, ab;
-      wave_find_bin<1024>(hst, remaining, &b, &ab);
-      if (tid == 0) { sh_bin = b; sh_above = ab; }
-    }
-    __syncthreads();
-    prefix |= sh_bin << shift;
-    mask |= 1023u << shift;
-    remaining -= (int)sh_above;
-    __syncthreads();  // hst is cleared again by the next pass
-  }
-  const uint32_t T = prefix;
-  const int need = remaining;  // keys equal to T to keep (>= 1), the lowest positions
-  // per slice: candidates above T and equal to T
-  for_each_cand([&](uint32_t key, int s2) {
-    if (key > T) atomicAdd(&s_gtT[s2], 1);
-    else if (key == T) atomicAdd(&s_eqT[s2], 1);
-  });
-  __syncthreads();
+  const uint32_t T = (uint32_t)sel[2 * head];
+  const int P = sel[2 * head + 1];
+  const int s_off = off[(size_t)head * ntk + sl];
+  const int kept_here = (sl + 1 < ntk ? off[(size_t)head * ntk + sl + 1] : k) - s_off;
   const bool direct = n - k < k;  // the head's evicted candidates are the fewer
-  if (tid == 0) {  // fixed order over the slices
-    int eb = 0, ob = 0;
-    for (int s2 = 0; s2 < ntk; ++s2) {
-      const int kept_s2 = s_gt[s2] + s_gtT[s2] + min(max(need - eb, 0), s_eqT[s2]);
-      if (s2 == sl) {
-        s_off = ob;
-        s_eqb = eb;
-        const int valid_s2 = min(TKS, n - s2 * TKS);
-        s_nrows = direct ? valid_s2 - kept_s2 : kept_s2;
-      }
-      ob += kept_s2;
-      eb += s_eqT[s2];
-    }
-  }
-  __syncthreads();
-  // the slice's kept positions, in order: one scan of (keys above T, keys at T) per
-  // thread, packed in 16-bit halves; the keys at T kept before a thread are the first of
-  // the need - (keys at T in earlier slices) still to keep
-  int n_gt = 0, n_eq = 0;
-#pragma unroll
-  for (int u = 0; u < TKPT; ++u) {
-    n_gt += valid[u] && key[u] > T;
-    n_eq += valid[u] && key[u] == T;
-  }
-  int tot;
-  const int before = block_excl_scan<TKT>(n_gt | (n_eq << 16), sW, &tot);
-  int eq_rank = s_eqb + (before >> 16);
+  // the slice's kept positions, in order
+  const int j0 = sl * TKS + TKPT * tid;
   bool keep[TKPT];
+  int n_keep = 0, tot;
 #pragma unroll
   for (int u = 0; u < TKPT; ++u) {
-    const bool eq = valid[u] && key[u] == T;
-    keep[u] = (valid[u] && key[u] > T) || (eq && eq_rank < need);
-    eq_rank += eq;
+    keep[u] = valid[u] && (key[u] > T || (key[u] == T && j0 + u <= P));
+    n_keep += keep[u];
   }
   // p = kept positions before the thread's current one, so a position that is not kept
   // is the (j - p)-th evicted one
-  int p = s_off + (before & 0xFFFF) + min(max(need - s_eqb, 0), before >> 16);
+  int p = s_off + block_excl_scan<TKT>(n_keep, sW, &tot);
   int32_t* o = out + (size_t)head * out_stride;
-  const int j0 = sl * TKS + TKPT * tid;
   const int e_off = sl * TKS - s_off;  // evicted positions before the slice
 #pragma unroll
   for (int u = 0; u < TKPT; ++u) {
     if (keep[u]) {
       if (p < k) {
         o[p] = j0 + u + pos_offset;
-        if (COV && !direct) s_rows[min(max(p - s_off, 0), TKS - 1)] = j0 + u + pos_offset;
+        if (!direct) s_rows[min(max(p - s_off, 0), TKS - 1)] = j0 + u + pos_offset;
       }
       ++p;
-    } else if (COV && valid[u] && direct) {  // not kept: the (j - p)-th evicted position
+    } else if (valid[u] && direct) {  // not kept: the (j - p)-th evicted position
       const int e = j0 + u - p;
       if (e >= 0 && e < n - k) s_rows[min(max(e - e_off, 0), TKS - 1)] = j0 + u + pos_offset;
     }
   }
-  if constexpr (COV) {
-    __syncthreads();
-    slice_cov<E, D>(a, head, sl, s_rows, min(s_nrows, TKS), direct ? 1.f : -1.f);
-  }
+  __syncthreads();
+  const int n_here = min(TKS, n - sl * TKS);
+  const int nrows = direct ? n_here - kept_here : kept_here;
+  slice_cov<E, D>(a, head, sl, s_rows, min(max(nrows, 0), TKS), direct ? 1.f : -1.f);
+}
+
+// Head-adaptive budgets, after k_tk_cand over the sequence's Hkv * n_c masses (position
+// head * n_c + j): the slice's kept positions counted per head into kh (zeroed before).
+__global__ void __launch_bounds__(TKT) k_tk_count(const float* __restrict__ scores, int n, int n_c,
+                                                    const int* __restrict__ sel,
+                                                    int32_t* kh, int Hkv) {
+  __shared__ int s_cnt[TKS];  // a slice of TKS positions touches at most as many heads
+  const int b = blockIdx.y, sl = blockIdx.x, tid = threadIdx.x;
+  uint32_t key[TKPT];
+  bool valid[TKPT];
+  slice_keys(scores + (size_t)b * n, n, sl, key, valid);
+  const uint32_t T = (uint32_t)sel[2 * b];
+  const int P = sel[2 * b + 1];
+  const int h0 = sl * TKS / n_c, nh = (min((sl + 1) * TKS, n) - 1) / n_c - h0 + 1;
+  for (int i = tid; i < nh; i += TKT) s_cnt[i] = 0;
+  __syncthreads();
+  const int j0 = sl * TKS + TKPT * tid;
+#pragma unroll
+  for (int u = 0; u < TKPT; ++u)
+    if (valid[u] && (key[u] > T || (key[u] == T && j0 + u <= P))) atomicAdd(&s_cnt[(j0 + u) / n_c - h0], 1);
+  __syncthreads();
+  for (int i = tid; i < nh; i += TKT)
+    if (s_cnt[i]) atomicAdd(kh + (size_t)b * Hkv + h0 + i, s_cnt[i]);
 }
 
 // ------------------------------------------------------------------------------------
@@ -1668,7 +1776,7 @@ __global__ void __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) k_residual(Compre
       const size_t o = (size_t)head * a.n_c + (j - c_lo);
       const float sc = a.abar[o] * sqrtf(sRes[x]);
       a.score[o] = sc;
-      atomicAdd(&sHist[score_key(sc) >> 20], 1u);
+      atomicAdd(&sHist[key_bin(score_key(sc))], 1u);
     }
   }
   __syncthreads();
@@ -1740,7 +1848,7 @@ __global__ void __launch_bounds__(256) k_zero_moments(CompressArgs a) {
   } while (0)
 
 // `which` selects the histogram the score producer filled (0: first selection, 1: final).
-// The selection's covariance slots are written by the same launch (k_tk_write<.., true>).
+// The selection's covariance slots are written by the same launch (k_tk_write).
 template <class T, int D>
 static hipError_t launch_topk(const CompressArgs& a, const float* scores, int which,
                               int32_t* out, hipStream_t st) {
@@ -1748,47 +1856,27 @@ static hipError_t launch_topk(const CompressArgs& a, const float* scores, int wh
   const dim3 grid(a.ntk, a.H);
   hipLaunchKernelGGL(k_tk_cand, grid, dim3(TKT), 0, st, scores, a.n_c, a.k_keep,
                      (const int*)a.kh, (const uint32_t*)(a.tk_hh + (size_t)which * a.H * TK_HBINS),
-                     a.tk_state, a.tk_cnt, a.tk_cand);
+                     a.tk_arr, a.tk_cnt, a.tk_cand, a.tk_sel, a.tk_off);
   MKV_CHECK_LAUNCH();
-  hipLaunchKernelGGL((k_tk_write<T, D, true>), grid, dim3(TKT), 0, st, scores, a.n_c, a.k_keep,
-                     (const int*)a.kh, (const int*)a.tk_state, (const int*)a.tk_cnt,
-                     (const uint32_t*)a.tk_cand, out, a.kmax, a.n_s, a);
+  hipLaunchKernelGGL((k_tk_write<T, D>), grid, dim3(TKT), 0, st, scores, a.n_c, a.k_keep,
+                     (const int*)a.kh, (const int*)a.tk_sel, (const int*)a.tk_off, out, a.kmax, a.n_s, a);
   MKV_CHECK_LAUNCH();
   return hipSuccess;
 }
 
 // Head-adaptive budgets: one layer-wide selection per sequence over the Hkv heads' abar
 // rows (contiguous in memory, position head * n_c + j), the Hkv * k_keep largest with
-// equal values in (head, position) order; then each head's share of them.
-__global__ void __launch_bounds__(64) k_ada_counts(CompressArgs a) {
-  const int b = blockIdx.x;
-  const int K = a.Hkv * a.k_keep;
-  const int32_t* o = a.kept_all + (size_t)b * K;
-  auto lower = [&](int x) {  // first index with o[i] >= x (o ascending)
-    int lo = 0, hi = K;
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (o[mid] < x) lo = mid + 1; else hi = mid;
-    }
-    return lo;
-  };
-  for (int h = threadIdx.x; h < a.Hkv; h += 64)
-    a.kh[(size_t)b * a.Hkv + h] = lower((h + 1) * a.n_c) - lower(h * a.n_c);
-}
-
+// equal values in (head, position) order; each head's share of them goes to kh.
 static hipError_t launch_head_budgets(const CompressArgs& a, hipStream_t st) {
   if (!a.adaptive || a.k_keep <= 0) return hipSuccess;
   const int n = a.Hkv * a.n_c, k = a.Hkv * a.k_keep;
   const dim3 grid(a.ntk_g, a.B);
   hipLaunchKernelGGL(k_tk_cand, grid, dim3(TKT), 0, st, (const float*)a.abar, n, k,
-                     (const int*)nullptr, (const uint32_t*)a.tk_hs, a.tk_state_g, a.tk_cnt_g,
-                     a.tk_cand_g);
+                     (const int*)nullptr, (const uint32_t*)a.tk_hs, a.tk_arr_g, a.tk_cnt_g,
+                     a.tk_cand_g, a.tk_sel_g, a.tk_off_g);
   MKV_CHECK_LAUNCH();
-  hipLaunchKernelGGL((k_tk_write<float, 64, false>), grid, dim3(TKT), 0, st, (const float*)a.abar, n, k,
-                     (const int*)nullptr, (const int*)a.tk_state_g, (const int*)a.tk_cnt_g,
-                     (const uint32_t*)a.tk_cand_g, a.kept_all, k, 0, a);
-  MKV_CHECK_LAUNCH();
-  hipLaunchKernelGGL(k_ada_counts, dim3(a.B), dim3(64), 0, st, a);
+  hipLaunchKernelGGL(k_tk_count, grid, dim3(TKT), 0, st, (const float*)a.abar, n, a.n_c,
+                     (const int*)a.tk_sel_g, a.kh, a.Hkv);
   MKV_CHECK_LAUNCH();
   return hipSuccess;
 }

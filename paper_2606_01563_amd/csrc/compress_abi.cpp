@@ -115,9 +115,11 @@ mkv::CompressArgs compress_layout(const mkv_compress_params* p, void* ws, size_t
   a.kept0 = c.take<int32_t>(H * a.kmax * sizeof(int32_t));
   a.kept = c.take<int32_t>(H * a.kmax * sizeof(int32_t));
   a.tk_hh = c.take<uint32_t>(2 * H * 2048 * sizeof(uint32_t));
-  a.tk_state = c.take<int32_t>(H * 2 * sizeof(int32_t));
-  a.tk_cnt = c.take<int32_t>(H * a.ntk * 2 * sizeof(int32_t));
-  a.tk_cand = c.take<uint32_t>(H * a.ntk * 2048 * sizeof(uint32_t));
+  a.tk_arr = c.take<int32_t>(H * sizeof(int32_t));
+  a.tk_cnt = c.take<uint64_t>(H * a.ntk * sizeof(uint64_t));
+  a.tk_sel = c.take<int32_t>(H * 2 * sizeof(int32_t));
+  a.tk_off = c.take<int32_t>(H * a.ntk * sizeof(int32_t));
+  a.tk_cand = c.take<uint64_t>(H * a.ntk * 2048 * sizeof(uint64_t));
   a.spart = c.take<float>(H * a.nslot * D * D * sizeof(float));
   a.svkpart = c.take<float>(H * a.nslot * 2 * D * sizeof(float));
   a.s0 = c.take<float>(H * D * D * sizeof(float));
@@ -126,11 +128,12 @@ mkv::CompressArgs compress_layout(const mkv_compress_params* p, void* ws, size_t
   if (a.adaptive) {
     const size_t Bs = a.B;
     a.kh = c.take<int32_t>(H * sizeof(int32_t));
-    a.kept_all = c.take<int32_t>(Bs * a.Hkv * std::max(a.k_keep, 1) * sizeof(int32_t));
     a.tk_hs = c.take<uint32_t>(Bs * 2048 * sizeof(uint32_t));
-    a.tk_state_g = c.take<int32_t>(Bs * 2 * sizeof(int32_t));
-    a.tk_cnt_g = c.take<int32_t>(Bs * a.ntk_g * 2 * sizeof(int32_t));
-    a.tk_cand_g = c.take<uint32_t>(Bs * a.ntk_g * 2048 * sizeof(uint32_t));
+    a.tk_arr_g = c.take<int32_t>(Bs * sizeof(int32_t));
+    a.tk_cnt_g = c.take<uint64_t>(Bs * a.ntk_g * sizeof(uint64_t));
+    a.tk_sel_g = c.take<int32_t>(Bs * 2 * sizeof(int32_t));
+    a.tk_off_g = c.take<int32_t>(Bs * a.ntk_g * sizeof(int32_t));
+    a.tk_cand_g = c.take<uint64_t>(Bs * a.ntk_g * 2048 * sizeof(uint64_t));
   }
   *total = c.off;
   return a;

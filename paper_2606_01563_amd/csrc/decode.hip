@@ -83,18 +83,6 @@ __device__ __forceinline__ float2 ld_agent2(const float* p) {
                                        __HIP_MEMORY_SCOPE_AGENT);
   return make_float2(__uint_as_float((uint32_t)u), __uint_as_float((uint32_t)(u >> 32)));
 }
-// s_waitcnt with vmcnt = 0 and the other counters at their maximum: every vector memory
-// operation of the wave issued so far (stores included) has completed.
-constexpr int kWaitVmem = 0x0F70;
-__device__ __forceinline__ void stores_complete() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_s_waitcnt(kWaitVmem);
-}
-__device__ __forceinline__ void loads_after_count() {
-  __builtin_amdgcn_s_waitcnt(kWaitVmem);
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
-
 // Query fragments of one KV head's group (A operand of Q.K^T, B operand of S_tilde q):
 // lane l holds 8 dims at 32 ks + 8 (l / 16) of query l % 16; queries past G are zero.
 template <class T, int D>

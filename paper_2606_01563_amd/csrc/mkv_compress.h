@@ -35,11 +35,14 @@ struct CompressArgs {
   float* score;             // [H, n_c]          moment-round score
   int32_t* kept0;           // [H, kmax]         provisional kept positions (ascending)
   int32_t* kept;            // [H, kmax]         final kept positions (ascending)
-  uint32_t* tk_hh;          // [2, H, 2048]      top-k: per-head histograms of key bits 30..20
-                            //                   of the first and the final scores
-  int32_t* tk_state;        // [H, 2]            top-k: bin of the k-th key, count above it
-  int32_t* tk_cnt;          // [H, ntk, 2]       top-k: per slice, keys above the bin, in it
-  uint32_t* tk_cand;        // [H, ntk, 2048]    top-k: per slice, the keys in the bin
+  uint32_t* tk_hh;          // [2, H, 2048]      top-k: per-head key histograms of the first
+                            //                   and the final scores
+  int32_t* tk_arr;          // [H]               top-k: slices arrived, zero between launches
+  uint64_t* tk_cnt;         // [H, ntk]          top-k: per slice, keys above the k-th key's
+                            //                   bin, and (high half) in it
+  uint64_t* tk_cand;        // [H, ntk, 2048]    top-k: (key, position) of the keys in the bin
+  int32_t* tk_sel;          // [H, 2]            top-k: the k-th key, the last equal position kept
+  int32_t* tk_off;          // [H, ntk]          top-k: per slice, output offset
   float* spart;             // [H, nslot, D, D]  covariance partials (after the row-statistics
                             // launch, slot 0 holds the sum of slots 0 .. nsl1 - 1)
   float* svkpart;           // [H, nslot, 2, D]  (s_v, s_k) partials
@@ -65,11 +68,12 @@ struct CompressArgs {
   // head-adaptive budgets (adaptive = 1): a per-sequence selection over the layer
   int adaptive;
   int32_t* kh;              // [H] candidates kept per head, or null (k_keep everywhere)
-  int32_t* kept_all;        // [B, Hkv*k_keep] layer-wide kept candidates (head*n_c + j)
   uint32_t* tk_hs;          // [B, 2048] key histogram of abar over the layer
-  int32_t* tk_state_g;      // [B, 2], and the candidate buffers of that selection:
-  int32_t* tk_cnt_g;        // [B, ntk_g, 2]
-  uint32_t* tk_cand_g;      // [B, ntk_g, 2048]
+  int32_t* tk_arr_g;        // [B], and the buffers of that selection:
+  uint64_t* tk_cnt_g;       // [B, ntk_g]
+  uint64_t* tk_cand_g;      // [B, ntk_g, 2048]
+  int32_t* tk_sel_g;        // [B, 2]
+  int32_t* tk_off_g;        // [B, ntk_g]
   int ntk_g;                // slices of the layer-wide selection
   int idx_stride;           // entries per head of idx_out
   float scale, tau;

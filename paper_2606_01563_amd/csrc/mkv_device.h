@@ -178,7 +178,52 @@ __device__ __forceinline__ float cross_row_max(float x) {
 __device__ __forceinline__ float wave_sum(float x) { return cross_row_sum(row16_sum(x)); }
 __device__ __forceinline__ float wave_max(float x) { return cross_row_max(row16_max(x)); }
 
+// Inclusive prefix sum over the 64 lanes through DPP (row shifts, then the row totals
+// broadcast into the rows after): no LDS round trips.
+template <int CTRL, int ROWS> __device__ __forceinline__ int dpp_rows_i(int x) {
+  return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ int wave_incl_scan(int x) {
+  x += dpp_rows_i<0x111, 0xF>(x);  // row_shr:1
+  x += dpp_rows_i<0x112, 0xF>(x);  // row_shr:2
+  x += dpp_rows_i<0x114, 0xF>(x);  // row_shr:4
+  x += dpp_rows_i<0x118, 0xF>(x);  // row_shr:8
+  x += dpp_rows_i<0x142, 0xA>(x);  // row_bcast:15 into rows 1 and 3
+  x += dpp_rows_i<0x143, 0xC>(x);  // row_bcast:31 into rows 2 and 3
+  return x;
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// ---------------------------------------------------------------- in-launch hand-off
+// Results that one workgroup hands to another of the same launch go through agent-scope
+// relaxed atomic stores and loads, which are not served from the per-XCD caches.  A writer
+// waits until its own stores have completed (stores_complete) before it counts itself in,
+// and the last to arrive reads only after the count (loads_after_count).
+// s_waitcnt with vmcnt = 0 and the other counters at their maximum: every vector memory
+// operation of the wave issued so far (stores included) has completed.
+constexpr int kWaitVmem = 0x0F70;
+__device__ __forceinline__ void stores_complete() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_s_waitcnt(kWaitVmem);
+}
+__device__ __forceinline__ void loads_after_count() {
+  __builtin_amdgcn_s_waitcnt(kWaitVmem);
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+__device__ __forceinline__ void st_agent_u32(uint32_t* p, uint32_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t ld_agent_u32(const uint32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void st_agent_u64(uint64_t* p, uint64_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint64_t ld_agent_u64(const uint64_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // Online (max, sum) pair in the base-2 domain: represents sum_i 2^(x_i) = l * 2^m.
 __device__ __forceinline__ void ml_merge(float& m, float& l, float m2, float l2) {

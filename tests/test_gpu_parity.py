@@ -392,6 +392,20 @@ def test_compress_and_decode_are_bit_deterministic():
     assert torch.equal(outs[0], outs[1])
 
 
+@pytest.mark.parametrize("log2_v,mi_rounds", [(-60, 0), (-60, 1), (40, 0)])
+def test_selection_with_scores_outside_the_histogram(log2_v, mi_rounds):
+    """Values scaled so that every score falls into an end bin of the key histogram (below
+    2^-28, above 2^4): the selection then refines whole keys over all candidates, three
+    slices of them."""
+    wl, cpu, gpu = layer("tiny_fp32_n2048", steps=1, dtype=torch.bfloat16, head_dim=128, ctx_len=5000,
+                         n_q_heads=4, n_kv_heads=2, window=16, budgets=(333,))
+    for x in (cpu, gpu):
+        x["v"] = x["v"] * 2.0 ** log2_v
+    out = P.run_compress(gpu, 333, cap=333, mi_rounds=mi_rounds)
+    for h in range(2):
+        announce(f"v * 2^{log2_v}: {P.check_compress_head(cpu, out, 0, h, 333, mi_rounds=mi_rounds)}")
+
+
 @pytest.mark.parametrize("ctx_len", [12000, 33000])
 @pytest.mark.parametrize("mi_rounds", [-1, 0])
 def test_selection_with_all_scores_equal_keeps_the_lowest_positions(ctx_len, mi_rounds):
