@@ -190,9 +190,10 @@ typedef struct {
                         /* per KV head; k > 1 = k token slices of one wave each      */
                         /* (rows rounded up to a multiple of 32), merged in the same */
                         /* launch by the last wave of the head to finish; 0 =        */
-                        /* automatic (one workgroup per KV head up to max_len 384,   */
-                        /* else about 768 slices in the whole grid).  One launch     */
-                        /* either way.                                               */
+                        /* automatic (by max_len and the number of heads: one        */
+                        /* workgroup per KV head, a few workgroups per head merged   */
+                        /* by the last to finish, or about 768 slices in the whole   */
+                        /* grid).  One launch either way.                            */
   int32_t summary;      /* form of the S argument: 0 = the raw sum S (fp32); 1 = the */
                         /* prepared form written by momentkv_prepare_summary; 2 =    */
                         /* its half-precision form (bf16 caches only); 3 = the raw   */

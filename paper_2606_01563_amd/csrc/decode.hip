@@ -1,7 +1,7 @@
 // Corrected decode attention over the retained cache (Algorithm 1 Phase 2; Eqs. fhat,
 // jensen and fused; log-domain mixing weight of App. C.2).
 //
-// Two launch shapes, chosen by the host from the cache length bound:
+// Three launch shapes, chosen by the host from the cache length bound and the head count:
 //
 // fused   k_decode_fused: one 4-wave workgroup per KV head, one launch.  Wave w computes
 //         rows [32w, 32w + 32) of S_tilde q (S_tilde = S - s_v s_k^T / n_e, clamped; formed
@@ -22,11 +22,16 @@
 //         on the head's counter, and the wave that completes the count merges the head:
 //         per query, the slices in a fixed order, then the new token, then the
 //         correction (so the result does not depend on which wave merges).
-//         Used for long caches: reading is bound by how much each CU keeps in flight, so
-//         the finishing time is set by the busiest CU, and thousands of short slices let
-//         the dispatcher balance a few hundred heads over 256 CUs.
+//         Used for long caches of many heads: reading is bound by how much each CU keeps
+//         in flight, so the finishing time is set by the busiest CU, and thousands of short
+//         slices let the dispatcher balance a few hundred heads over 256 CUs.
 //
-// Common to both: Q.K^T and P.V run on MFMA over 32-token blocks (the G queries padded to
+// group   k_decode_group: as split, with workgroups of 4 or 8 waves that merge their waves'
+//         states in LDS first, so that few partials per head are left to the last one to
+//         finish.  Used for longer caches of few heads, where a call is a chain of round
+//         trips and the merge of many slices by one wave was half of it.
+//
+// Common to all: Q.K^T and P.V run on MFMA over 32-token blocks (the G queries padded to
 // 16 rows) with the online softmax in the base-2 domain.  The new token (k_new, v_new) is
 // written to row lens of the cache by the wave whose range holds that row and is attended
 // to from k_new / v_new, so no cache read depends on the append.
@@ -77,6 +82,9 @@ __device__ __forceinline__ void st_agent(float* p, float v) {
 __device__ __forceinline__ void st_agent2(float* p, float x, float y) {
   const uint64_t u = (uint64_t)__float_as_uint(x) | ((uint64_t)__float_as_uint(y) << 32);
   __hip_atomic_store(reinterpret_cast<uint64_t*>(p), u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float ld_agent(const float* p) {
+  return __uint_as_float(ld_agent_u32(reinterpret_cast<const uint32_t*>(p)));
 }
 __device__ __forceinline__ float2 ld_agent2(const float* p) {
   const uint64_t u = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED,
@@ -901,9 +909,175 @@ k_decode_slice(DecodeArgs a) {
   merge_head<T, D>(a, head, lane);
 }
 
+// ---------------------------------------------------------------- group launch
+// Few heads: one launch of NW-wave workgroups, per head one for S_tilde q and nsplit token
+// groups of split_len rows.  A group's waves take its 32-row blocks w, w + NW, ... (a block
+// is about 1.5 us of dependent work for its wave, so more waves rather than more blocks in
+// flight: a second register set measured slower) and merge their states in LDS, so a head has at most kMaxGroups partials, which the last workgroup
+// of the head to arrive reads in one round trip (one query per wave).
+template <class T, int D, int GMAX, int PREP, int NW>
+__global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_decode_group(DecodeArgs a) {
+  typedef BlockAttn<T, D, GMAX> BA;
+  constexpr int CPL = D / 64, KS = D / 32;
+  constexpr int VT_BYTES = (int)sizeof(typename BA::VtTile);
+  static_assert(VT_BYTES >= GMAX * D * 4, "o rows fit in the V tile");
+  __shared__ __align__(16) unsigned char s_vt[NW][VT_BYTES];
+  __shared__ __align__(16) T s_p[NW][16][BA::TB + BA::PT];
+  __shared__ float s_ml[NW][GMAX * 2];
+  __shared__ int s_last;
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n_sq = a.nsq > 0 ? a.n_heads : 0;  // the S_tilde q workgroups come first
+  const bool is_sq = (int)blockIdx.x < n_sq;
+  const int idx = is_sq ? (int)blockIdx.x : (int)blockIdx.x - n_sq;
+  const int head = is_sq ? idx : idx / a.nsplit;
+  const int G = a.G;
+  const T* qh = reinterpret_cast<const T*>(a.q) + (size_t)head * G * D;
+  typename BA::FragT qf[KS];
+  if (is_sq) {
+    if (32 * wave < D) {
+      SqRows<T, D, PREP> sq;
+      sq.load(a, head, 32 * wave, lane);
+      load_query_frags<T, D>(qh, G, lane, qf);
+      sq.template compute<true>(a, qf, 32 * wave, lane, a.sq + (size_t)head * G * D);
+    }
+  } else {
+    const int split = idx % a.nsplit;
+    const int t0 = split * a.split_len;
+    typename BA::VtTile& vt = *reinterpret_cast<typename BA::VtTile*>(s_vt[wave]);
+    BA ba;
+    ba.kc = reinterpret_cast<const T*>(a.k_cache) + (size_t)head * a.cap * D;
+    ba.vc = reinterpret_cast<const T*>(a.v_cache) + (size_t)head * a.cap * D;
+    ba.init();
+    // the wave's first block is requested together with lens, bounded by the capacity only;
+    // V rows past the end are cleared once lens is known, their logits masked
+    const int j_first = t0 + BA::TB * wave;
+    ba.t_end = min(a.cap, t0 + a.split_len);
+    ba.load(j_first, lane);
+    load_query_frags<T, D>(qh, G, lane, qf);
+    const HeadLen hl = head_len(a, a.lens[head]);
+    ba.t_end = max(t0, min(t0 + a.split_len, hl.cache_len));
+    if (j_first + BA::TB > ba.t_end) ba.clear_v_past_end(j_first, lane);
+    if (a.k_new != nullptr && !hl.can_append && split == 0 && threadIdx.x == 0) atomicOr(a.flag, 1);
+    ba.run(qf, j_first, NW * BA::TB, a.scale * kLog2e, G, lane, vt, s_p[wave]);
+    wave_lds_order();
+    ba.store_lds(reinterpret_cast<float*>(s_vt[wave]), s_ml[wave], G, lane);
+    // the group whose range holds row old_len (the last one for rows past the split)
+    if (wave == NW - 1 && hl.can_append && min(hl.old_len / a.split_len, a.nsplit - 1) == split)
+      append_row<T, D>(a, head, hl.old_len, lane);
+    __syncthreads();
+    if (t0 < ba.t_end) {  // an empty group writes nothing: the merge skips it
+      for (int g = wave; g < G; g += NW) {
+        float M = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) M = fmaxf(M, s_ml[w][2 * g]);
+        float l = 0.f, o[CPL];
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) o[c] = 0.f;
+        if (M != -INFINITY) {
+#pragma unroll
+          for (int w = 0; w < NW; ++w) {
+            const float wt = fast_exp2(s_ml[w][2 * g] - M);
+            l += s_ml[w][2 * g + 1] * wt;
+            const float* so = reinterpret_cast<const float*>(s_vt[w]) + g * D + lane * CPL;
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) o[c] += so[c] * wt;
+          }
+        }
+        const size_t pb = ((size_t)head * a.nsplit + split) * G + g;
+        if constexpr (CPL == 2) st_agent2(a.part_o + pb * D + 2 * lane, o[0], o[CPL - 1]);
+        else st_agent(a.part_o + pb * D + lane, o[0]);
+        if (lane == 0) st_agent2(a.part_ml + pb * 2, M, l);
+      }
+    }
+  }
+  // count in; the last workgroup of the head merges it
+  stores_complete();
+  __syncthreads();
+  if (threadIdx.x == 0) s_last = atomicAdd(a.cnt + head, 1) == (n_sq > 0) + a.nsplit - 1;
+  __syncthreads();
+  if (!s_last) return;
+  loads_after_count();
+  const HeadLen hl = head_len(a, a.lens[head]);
+  const int ne = a.n_e[head];
+  const int n_live = live_slices(a, hl.cache_len), last = max(n_live, 1) - 1;
+  for (int g = wave; g < G; g += NW) {
+    // every read of the query before the first reduction
+    const size_t pb = (size_t)head * a.nsplit;
+    const float2 ml = ld_agent2(a.part_ml + ((pb + min(lane, last)) * G + g) * 2);
+    float ov[kMaxGroups][CPL], sqv[CPL];
+    auto fetch = [&](int s) {  // groups past the live ones repeat the last, unused
+      const float* p = a.part_o + ((pb + min(s, last)) * G + g) * D + lane * CPL;
+      if constexpr (CPL == 2) {
+        const float2 t = ld_agent2(p);
+        ov[s][0] = t.x;
+        ov[s][CPL - 1] = t.y;
+      } else {
+        ov[s][0] = ld_agent(p);
+      }
+    };
+#pragma unroll
+    for (int s = 0; s < 4; ++s) fetch(s);
+    if (n_live > 4) {
+#pragma unroll
+      for (int s = 4; s < kMaxGroups; ++s) fetch(s);
+    }
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) sqv[c] = 0.f;
+    if (n_sq > 0) {
+      const float* p = a.sq + ((size_t)head * G + g) * D + lane * CPL;
+      if constexpr (CPL == 2) {
+        const float2 t = ld_agent2(p);
+        sqv[0] = t.x;
+        sqv[CPL - 1] = t.y;
+      } else {
+        sqv[0] = ld_agent(p);
+      }
+    }
+    const QueryCols<CPL> qc = load_query_cols<T, D>(a, head, g, lane);
+    const bool live = lane < n_live;
+    const float M = wave_max(live ? ml.x : -INFINITY);
+    const float w = (live && M != -INFINITY) ? fast_exp2(ml.x - M) : 0.f;
+    const float l = wave_sum(live ? ml.y * w : 0.f);
+    float o[CPL];
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) o[c] = 0.f;
+    auto add = [&](int s) {  // what was read for a group past the live ones may be anything
+      const float ws = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), s));
+#pragma unroll
+      for (int c = 0; c < CPL; ++c) o[c] += s < n_live ? ws * ov[s][c] : 0.f;
+    };
+#pragma unroll
+    for (int s = 0; s < 4; ++s) add(s);
+    if (n_live > 4) {
+#pragma unroll
+      for (int s = 4; s < kMaxGroups; ++s) add(s);
+    }
+    finish_query<T, D>(a, head, g, lane, M, l, o, qc, sqv, n_sq > 0, ne, hl.can_append);
+  }
+  if (threadIdx.x == 0) {
+    // every other workgroup of the head has counted itself in, and so has read lens
+    __hip_atomic_store(a.cnt + head, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();  // every wave has read lens
+  if (threadIdx.x == 0 && hl.can_append) a.lens[head] = hl.old_len + 1;
+}
+
 template <class T, int D, int GMAX, int PREP>
 static hipError_t launch_decode_p(const DecodeArgs& a, hipStream_t st) {
-  if (a.fused) {
+  if (a.shape == kDecodeGroup) {
+    const unsigned wgs = (unsigned)a.n_heads * (unsigned)((a.nsq > 0) + a.nsplit);
+    if constexpr (sizeof(T) == 2) {
+      if (a.split_len >= kGroupWideLen) {
+        hipLaunchKernelGGL((k_decode_group<T, D, GMAX, PREP, 8>), dim3(wgs), dim3(512), 0, st, a);
+        return hipGetLastError();
+      }
+    }
+    hipLaunchKernelGGL((k_decode_group<T, D, GMAX, PREP, 4>), dim3(wgs), dim3(256), 0, st, a);
+    return hipGetLastError();
+  }
+  if (a.shape == kDecodeFused) {
     hipLaunchKernelGGL((k_decode_fused<T, D, GMAX, PREP>), dim3(a.n_heads), dim3(256), 0, st, a);
     return hipGetLastError();
   }

@@ -17,27 +17,55 @@ namespace {
 
 constexpr int64_t kDecodeWaves = 768;      // target slice count of an automatic decode split
 constexpr int64_t kMaxDecodeWaves = 1 << 24;  // decode grid limit (single-wave workgroups)
-constexpr int kFusedMaxLen = 384;          // automatic decode: single launch up to this length
+// Automatic shape (n_split = 0).  Measured with G = 4, d = 128, bf16, the prepared summary,
+// calls replayed back to back, us per call (one workgroup per head / slices / groups):
+//   8 heads    256 rows  8.7 /  8.2 /  8.8    512 rows 12.1 / 10.1 /  8.8
+//             1024 rows 19.0 / 14.5 /  9.6   2048 rows   -  / 23.5 / 10.4
+//   16 heads  1024 rows 19.5 / 18.8 / 10.6   4096 rows   -  / 25.8 / 14.9
+//   32 heads   512 rows 12.7 / 13.3 /  9.6   2048 rows   -  / 19.2 / 14.4
+//   64 heads   384 rows 11.4 / 14.8 / 10.3   1024 rows 20.0 / 17.2 / 14.0
+//             2048 rows   -  / 21.6 / 19.7   4096 rows   -  / 29.6 / 33.8
+//   128 heads  512 rows 13.4 / 16.6 / 16.4   1024 rows 20.5 / 21.3 / 21.4
+//   256 heads  512 rows 17.3 / 21.0 / 22.5   1024 rows 26.7 / 29.9 / 35.8
+//   288 heads  384 rows 21.2 / 20.7 / 25.4    512 rows 25.7 / 24.1 / 30.0
+// Up to 256 rows every head runs in one workgroup.  Longer caches of few heads: the
+// smallest group length (a multiple of 128 rows, to 768) that keeps the launch at kGroupWgs
+// token workgroups, so that with the heads' S_tilde q workgroups each starts at once on a
+// CU of its own.  Heads that fill the CUs at most once and caches that are short enough:
+// one workgroup per head, which needs no hand-off.  Else slices.
+constexpr int kFusedMaxLen = 256;
+constexpr int kFusedMaxLenMany = 384;
+constexpr int kFusedMaxLenFull = 1024;  // up to kCUs heads
+constexpr int kCUs = 256;
+constexpr int kGroupWgs = 192, kGroupMaxLen = 768;
 
 // ----------------------------------------------------------------------- decode
-// Token slices per KV head.  Automatic (n_split = 0): about kDecodeWaves single-wave
+// Token slices per KV head.  Slices shape with n_split = 0: about kDecodeWaves single-wave
 // slices in the whole grid (three per CU), at least 32 rows each.  Measured on a 288-head
 // stack, longer slices (fewer partials to merge) beat finer splits once every CU holds a
 // few slices.  Rows per slice are a multiple of the 32-row block.
-void decode_split(const mkv_decode_params* p, int* split_len, int* nsplit) {
+mkv::DecodeShape decode_shape(const mkv_decode_params* p, int* split_len, int* nsplit) {
   const int64_t heads = (int64_t)p->batch * p->n_kv_heads;
+  if (p->n_split == 0 && p->max_len > kFusedMaxLen) {
+    for (int gl = 128; gl <= kGroupMaxLen; gl += 128) {
+      const int n = ceil_div(p->max_len, gl);
+      if (n > 1 && n <= mkv::kMaxGroups && heads * n <= kGroupWgs) {
+        *split_len = gl;
+        *nsplit = n;
+        return mkv::kDecodeGroup;
+      }
+    }
+  }
   const int want = p->n_split > 0 ? p->n_split
                                   : (int)std::min<int64_t>(std::max<int64_t>((kDecodeWaves + heads - 1) / heads, 1), 1 << 20);
   int sl = ceil_div(p->max_len, want);
   sl = std::max(32, ceil_div(sl, 32) * 32);
   *split_len = sl;
   *nsplit = ceil_div(p->max_len, sl);
-}
-
-// One workgroup per KV head (single launch) for n_split = 1, or automatically for short
-// caches, where a call is bound by latency rather than by how the heads spread over CUs.
-bool decode_fused(const mkv_decode_params* p) {
-  return p->n_split == 1 || (p->n_split == 0 && p->max_len <= kFusedMaxLen);
+  if (p->n_split == 1) return mkv::kDecodeFused;
+  if (p->n_split == 0 && (p->max_len <= kFusedMaxLenMany || (heads <= kCUs && p->max_len <= kFusedMaxLenFull)))
+    return mkv::kDecodeFused;
+  return mkv::kDecodeSlices;
 }
 
 }  // namespace
@@ -62,7 +90,7 @@ mkv_status check_decode_params(const mkv_decode_params* p) {
   if (p->max_len < 1 || p->max_len > p->cap) return MKV_ERR_CAPACITY;
   // grid of single-wave workgroups: B * Hkv * (slices + covariance waves)
   int split_len = 0, nsplit = 0;
-  decode_split(p, &split_len, &nsplit);
+  decode_shape(p, &split_len, &nsplit);
   const int64_t waves = (int64_t)p->batch * p->n_kv_heads * (nsplit + p->head_dim / 32);
   if (waves > kMaxDecodeWaves) return MKV_ERR_UNSUPPORTED;
   return MKV_OK;
@@ -80,8 +108,7 @@ mkv::DecodeArgs decode_layout(const mkv_decode_params* p, void* ws, size_t* tota
   a.order = p->order;
   a.scale = p->scale > 0.f ? p->scale : 1.0f / std::sqrt((float)p->head_dim);
   a.tau = p->tau;
-  decode_split(p, &a.split_len, &a.nsplit);
-  a.fused = decode_fused(p) ? 1 : 0;
+  a.shape = decode_shape(p, &a.split_len, &a.nsplit);
   a.nsq = p->order >= 1 ? p->head_dim / 32 : 0;
   a.summary = p->summary;
   const size_t H = a.n_heads, D = p->head_dim, G = a.G;

@@ -7,6 +7,12 @@
 
 namespace mkv {
 
+// Launch shapes: one workgroup per KV head; single-wave token slices; token
+// groups of 4- or 8-wave workgroups (8 from kGroupWideLen rows, bf16).
+enum DecodeShape { kDecodeSlices = 0, kDecodeFused = 1, kDecodeGroup = 2 };
+constexpr int kMaxGroups = 16;  // partials per head of the group shape
+constexpr int kGroupWideLen = 256;
+
 struct DecodeArgs {
   const void* q;            // [B, Hq, D]
   void* k_cache;            // [B, Hkv, cap, D]
@@ -30,8 +36,8 @@ struct DecodeArgs {
   int n_heads;              // B * Hkv
   int n_pairs;              // B * Hq
   int Hkv, G, cap;
-  int fused;                // 1: one workgroup per KV head, single launch
-  int nsplit, split_len;    // split launch: token slices per KV head, rows per slice (x 32)
+  int shape;                // DecodeShape
+  int nsplit, split_len;    // token slices (groups) per KV head, rows per slice (x 32)
   int nsq;                  // S_tilde q waves per KV head (D / 32 rows each; 0 at order 0)
   int summary;              // 0: raw fp32 S; 1, 2: prepared forms; 3: raw bf16 S
   int order;

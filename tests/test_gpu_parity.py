@@ -197,6 +197,53 @@ def test_decode_single_launch_block_rounds(d, dtype, cap):
     P.run_decode_steps(gpu, out, 3, n_split=1, lens0=lens0, summary=1)
 
 
+@pytest.mark.parametrize("cap,append", [(300, True), (300, False), (1500, True)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("d", [64, 128])
+def test_decode_token_groups(d, dtype, cap, append):
+    """Few heads and more than 256 rows (automatic: token groups of 128 rows merged by the
+    last workgroup of the head): lengths on both sides of the group and block boundaries,
+    an empty head, appends landing on a group's first row, up to 12 groups."""
+    L = cap - 3
+    wl, cpu, gpu = layer("tiny_fp32_n2048", steps=3, dtype=dtype, head_dim=d, ctx_len=max(1000, cap + 300),
+                         batch=3, n_q_heads=6, n_kv_heads=2, window=16, budgets=(L,))
+    out = P.run_compress(gpu, L, cap=cap)
+    lens0 = ([[0, 127], [128, 160], [255, 297]] if cap == 300
+             else [[0, 1], [640, 1407], [1279, 1497]])
+    announce(f"token groups d={d} {dtype} cap={cap} lengths {lens0} append={append}")
+    P.run_decode_steps(gpu, out, 3, n_split=0, append=append, lens0=lens0, summary=int(append))
+
+
+@pytest.mark.parametrize("G", [8, 16])
+def test_decode_token_groups_repeat_bit_exact(G):
+    """The group shape on poisoned partials: calls repeated on one workspace (zeroed prefix,
+    the rest NaN) give the same bits, agree with the single workgroup, and leave the arrival
+    counters at zero; the no-workspace entry point gives the same bits."""
+    g = torch.Generator(device="cuda").manual_seed(9)
+    Hkv, d, cap = 5, 128, 517
+    r = lambda *s: torch.randn(*s, device="cuda", generator=g)
+    kc, vc = r(1, Hkv, cap, d).to(torch.bfloat16), r(1, Hkv, cap, d).to(torch.bfloat16)
+    q = r(1, Hkv * G, d).to(torch.bfloat16)
+    lens = torch.tensor([[0, 1, 128, 385, 517]], dtype=torch.int32, device="cuda")
+    n_e = torch.tensor([[0, 900, 1, 0, 40]], dtype=torch.int32, device="cuda")
+    args = (q, kc, vc, lens, n_e, r(1, Hkv, d) * 30, r(1, Hkv, d) * 30, r(1, Hkv, d, d) * 50)
+    ref = None
+    for rep in range(12):
+        if rep % 4 == 0:
+            p = mk.decode_params(q, kc, max_len=cap)
+            ws = torch.full((mk.momentkv_decode_workspace_bytes(p),), 0xFF, dtype=torch.uint8, device="cuda")
+            ws[:mk.momentkv_decode_workspace_zero_bytes(p)] = 0
+        o = mk.momentkv_decode_attn(*args, max_len=cap, workspace=ws)[0]
+        ref = o.clone() if ref is None else ref
+        assert torch.equal(o, ref), rep
+        assert int(ws[256:256 + 4 * Hkv].view(torch.int32).abs().sum()) == 0
+    one = mk.momentkv_decode_attn(*args, max_len=cap, n_split=1)[0].float()
+    rel = (one - ref.float()).norm(dim=-1) / one.norm(dim=-1).clamp_min(1e-30)
+    assert float(rel.max()) < 2e-2
+    na = mk.momentkv_decode_attn_noalloc(*args, max_len=cap, out=torch.empty_like(q))
+    assert torch.equal(na, ref)
+
+
 # ---------------------------------------------------------------- edge cases
 @pytest.mark.parametrize("summary", [0, 1])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
