@@ -35,8 +35,9 @@
 // 16 rows) with the online softmax in the base-2 domain.  The new token (k_new, v_new) is
 // written to row lens of the cache by the wave whose range holds that row and is attended
 // to from k_new / v_new, so no cache read depends on the append.
-#include "mkv_device.h"
+#include "mkv_bf16.h"
 #include "mkv_decode.h"
+#include "mkv_device.h"
 
 namespace mkv {
 
@@ -92,11 +93,12 @@ __device__ __forceinline__ float2 ld_agent2(const float* p) {
   return make_float2(__uint_as_float((uint32_t)u), __uint_as_float((uint32_t)(u >> 32)));
 }
 // Query fragments of one KV head's group (A operand of Q.K^T, B operand of S_tilde q):
-// lane l holds 8 dims at 32 ks + 8 (l / 16) of query l % 16; queries past G are zero.
+// lane l holds 8 dims at 32 ks + 8 (l / 16) of query query_of(l % 16); queries past G are
+// zero.
 template <class T, int D>
 __device__ __forceinline__ void load_query_frags(const T* qh, int G, int lane,
                                                  typename Frag<T>::type (&qf)[D / 32]) {
-  const int g = lane & 15, gc = min(g, G - 1);
+  const int g = query_of(lane & 15), gc = min(g, G - 1);
 #pragma unroll
   for (int ks = 0; ks < D / 32; ++ks) {
     const typename Frag<T>::type f = load_frag(qh + (size_t)gc * D + 32 * ks + 8 * (lane >> 4));
@@ -122,7 +124,7 @@ __device__ __forceinline__ void append_row(const DecodeArgs& a, int head, int ro
 
 // ---------------------------------------------------------------- S_tilde q
 // Rows [r0, r0 + 32) of S_tilde q (unscaled) for the queries held in the query fragments
-// (query g in MFMA column g).  load() issues every read; compute() writes result (g, r) to
+// (query query_of(c) in MFMA column c).  load() issues every read; compute() writes result (g, r) to
 // dst[g * D + r] for g < G.  Four forms of the summary:
 //  * raw S (PREP = false): fp32 MFMA; S_tilde = S - s_v s_k^T / n_e, clamped at tau, is
 //    formed as the rows are loaded;
@@ -193,7 +195,7 @@ struct SqRows {
   template <bool AGENT = false>
   __device__ __forceinline__ void compute(const DecodeArgs& a, const typename Frag<T>::type (&qf)[KS],
                                           int r0, int lane, float* dst) {
-    const int g = lane & 15;
+    const int g = query_of(lane & 15);
     f32x4 acc[2];
     if constexpr (HILO) {
 #pragma unroll
@@ -301,7 +303,7 @@ __global__ void __launch_bounds__(256) k_prepare_summary(DecodeArgs a, void* pre
 // ---------------------------------------------------------------- block attention
 // One wave's online-softmax attention over 32-row blocks of one KV head's cache rows
 // below t_end, for the G queries of the group:
-//  * K rows are MFMA B fragments of Q.K^T (lane: row (lane%16) + 16h, 8 dims at
+//  * K rows are MFMA B fragments of Q.K^T (lane: row 2 (lane%16) + h, 8 dims at
 //    8*(lane/16) + 32*ks);
 //  * V rows are loaded as token pairs (lane: rows 2p, 2p+1 with p = lane%16, 8-column
 //    groups lane/16 + 4c) and written to the wave's LDS tile as they are (bf16; read back
@@ -311,14 +313,15 @@ __global__ void __launch_bounds__(256) k_prepare_summary(DecodeArgs a, void* pre
 //    runs on MFMA: out[g][dim] in the same lane layout as the logits, so the online
 //    softmax rescale needs no shuffles.
 // The next block's rows are requested once the current ones have left the registers.
-// Lane l ends with rows g = 4 (l / 16) + i: (m_run[i], l_run[i]) in log2 units and
-// o[g][16 nt + l % 16] = oacc[nt][i].
+// Lane l ends with the queries g = 4 i + l / 16, i < NI: (m_run[i], l_run[i]) in log2 units
+// and o[g][16 nt + l % 16] = oacc[nt][i].
 template <class T, int D, int GMAX>
 struct BlockAttn {
   static constexpr int KS = D / 32;        // MFMA contraction steps per row
   static constexpr int TB = 32;            // tokens per block
   static constexpr int NVC = D / 32;       // V chunks (16 or 32 bytes) per lane and token
   static constexpr int NT = D / 16;        // 16-column output tiles of P.V
+  static constexpr int NI = GMAX / 4;      // queries per lane
   static constexpr int PT = 16 / (int)sizeof(T);  // LDS row padding (16 bytes)
   static constexpr bool TR = sizeof(T) == 2;       // bf16: V kept in its own layout
   static constexpr int LDV = D + 16;               // bf16 V rows padded by 32 bytes
@@ -332,7 +335,7 @@ struct BlockAttn {
   const T* vc;
   int t_end;
   FragT kf[2][KS], vf[2][NVC];
-  float m_run[4], l_run[4];
+  float m_run[NI], l_run[NI];
   f32x4 oacc[NT];
 
   // Rows at or past t_end are loaded from row t_end - 1 (row 0 when t_end = 0), so no
@@ -342,7 +345,7 @@ struct BlockAttn {
     const int last = max(t_end, 1) - 1;
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
-      const int j = min(j0 + 16 * hh + (lane & 15), last);
+      const int j = min(j0 + 2 * (lane & 15) + hh, last);
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
         kf[hh][ks] = load_frag(kc + (size_t)j * D + 32 * ks + 8 * (lane >> 4));
@@ -368,7 +371,7 @@ struct BlockAttn {
 
   __device__ __forceinline__ void init() {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) { m_run[i] = -INFINITY; l_run[i] = 0.f; }
+    for (int i = 0; i < NI; ++i) { m_run[i] = -INFINITY; l_run[i] = 0.f; }
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) oacc[nt] = zero4();
   }
@@ -376,9 +379,9 @@ struct BlockAttn {
   // Blocks at j_first, j_first + stride, ... below t_end; load(j_first) was issued.
   __device__ __forceinline__ void run(const FragT (&qf)[KS], int j_first, int stride, float c2,
                                       int G, int lane, VtTile& vt, PTile& sp) {
-    const int gbase = 4 * (lane >> 4);
+    const int q4 = lane >> 4, r16 = lane & 15;
     for (int j0 = j_first; j0 < t_end; j0 += stride) {
-      // ---- logits for the two 16-token halves
+      // ---- logits of the lane's two tokens
       f32x4 acc[2];
 #pragma unroll
       for (int hh = 0; hh < 2; ++hh) {
@@ -404,15 +407,15 @@ struct BlockAttn {
         }
       }
       if (j0 + stride < t_end) load(j0 + stride, lane);
-      // ---- online softmax over the 32 tokens (rows g = gbase + i)
-      float alpha[4];
+      // ---- online softmax over the 32 tokens
+      float alpha[NI];
       bool grew = false;
+      const int ja = j0 + 2 * r16;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int ja = j0 + (lane & 15), jb = ja + 16;
-        const bool gok = gbase + i < G;
+      for (int i = 0; i < NI; ++i) {
+        const bool gok = 4 * i + q4 < G;
         const float xa = (ja < t_end && gok) ? acc[0][i] * c2 : -INFINITY;
-        const float xb = (jb < t_end && gok) ? acc[1][i] * c2 : -INFINITY;
+        const float xb = (ja + 1 < t_end && gok) ? acc[1][i] * c2 : -INFINITY;
         const float bm = row16_max(fmaxf(xa, xb));
         const float mn = fmaxf(m_run[i], bm);
         float pa = 0.f, pb = 0.f;
@@ -426,21 +429,21 @@ struct BlockAttn {
         grew |= mn != m_run[i];
         l_run[i] = l_run[i] * alpha[i] + row16_sum(pa + pb);
         m_run[i] = mn;
-        if (gbase + i < GMAX) {
-          sp[gbase + i][lane & 15] = from_f<T>(pa);
-          sp[gbase + i][16 + (lane & 15)] = from_f<T>(pb);
-        }
+        if constexpr (sizeof(T) == 2)
+          *reinterpret_cast<uint32_t*>(&sp[4 * q4 + i][2 * r16]) = bf16_pair(pa, pb);
+        else
+          *reinterpret_cast<float2*>(&sp[4 * q4 + i][2 * r16]) = make_float2(pa, pb);
       }
       wave_lds_order();  // P and V are in LDS before they are read back
-      // ---- O = alpha * O + P . V on MFMA (A = P rows g, B = V); alpha is exactly 1
-      // where no running max grew, so the rescale is skipped when none did in the wave
+      // ---- O = alpha * O + P . V on MFMA (A = P rows, B = V); alpha is exactly 1 where
+      // no running max grew, so the rescale is skipped when none did in the wave
       const bool rescale = __any(grew);
-      const FragT pfr = ((lane & 15) < G) ? load_frag(&sp[lane & 15][8 * (lane >> 4)]) : zero_frag<T>();
+      const FragT pfr = query_of(r16) < G ? load_frag(&sp[r16][8 * q4]) : zero_frag<T>();
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
         if (rescale) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) oacc[nt][i] *= alpha[i];
+          for (int i = 0; i < NI; ++i) oacc[nt][i] *= alpha[i];
         }
         if constexpr (TR)
           mma(oacc[nt], pfr, lds_frag_tr(&vt[0][0], LDV, 0, 16 * nt, lane));
@@ -452,15 +455,15 @@ struct BlockAttn {
 
   // o rows g < G to so[g * D + col] (a wave-private float buffer), max/sum to ml[g * 2].
   __device__ __forceinline__ void store_lds(float* so, float* ml, int G, int lane) {
-    const int gbase = 4 * (lane >> 4);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if (gbase + i < G) {
+    for (int i = 0; i < NI; ++i) {
+      const int g = 4 * i + (lane >> 4);
+      if (g < G) {
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) so[(gbase + i) * D + 16 * nt + (lane & 15)] = oacc[nt][i];
+        for (int nt = 0; nt < NT; ++nt) so[g * D + 16 * nt + (lane & 15)] = oacc[nt][i];
         if ((lane & 15) == 0) {
-          ml[(gbase + i) * 2 + 0] = m_run[i];
-          ml[(gbase + i) * 2 + 1] = l_run[i];
+          ml[g * 2 + 0] = m_run[i];
+          ml[g * 2 + 1] = l_run[i];
         }
       }
     }

@@ -221,12 +221,13 @@ struct QueryRows {
 };
 
 // ---------------------------------------------------------------- attention of a wave
-// Online-softmax attention state of one wave over its blocks; query g = 4 (l / 16) + i
-// sits in MFMA row g, lane l holding entry i.
+// Online-softmax attention state of one wave over its blocks; lane l holds the queries
+// g = 4 i + l / 16, i < NI (query_of gives their MFMA rows).
 template <class T, int D, int GM>
 struct EvAttn {
   static constexpr int KS = D / 32;
   static constexpr int NOT = D / 16;              // 16-column output tiles of P.V
+  static constexpr int NI = GM / 4;               // queries per lane
   static constexpr int PT = 16 / (int)sizeof(T);  // LDS row padding (16 bytes)
   static constexpr int QRS = D + 16 / (int)sizeof(T);
   static constexpr bool TR = sizeof(T) == 2;       // bf16: V kept in its own layout
@@ -238,33 +239,33 @@ struct EvAttn {
   typedef T PTile[GM][kEvTB + PT];
   static_assert(sizeof(VtTile) >= GM * D * sizeof(float), "o rows fit in the V tile");
 
-  float m_run[4], l_run[4];
+  float m_run[NI], l_run[NI];
   f32x4 oacc[NOT];
 
   __device__ __forceinline__ void init() {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) { m_run[i] = -INFINITY; l_run[i] = 0.f; }
+    for (int i = 0; i < NI; ++i) { m_run[i] = -INFINITY; l_run[i] = 0.f; }
 #pragma unroll
     for (int nt = 0; nt < NOT; ++nt) oacc[nt] = zero4();
   }
 
-  // Base-2 logits c2 q_g . k of the rows j0 + 2 (l % 16) + hh in x[hh] (queries from LDS).
+  // Base-2 logits c2 q_g . k of the rows j0 + 2 (l % 16) + hh in x[hh][i] (queries from LDS).
   static __device__ __forceinline__ void logits(const T* s_q, const FragT (&kf)[2][KS], float c2,
-                                                int lane, f32x4 (&x)[2]) {
+                                                int lane, float (&x)[2][NI]) {
     const int r16 = lane & 15, q4 = lane >> 4;
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
       f32x4 acc = zero4();
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) mma(acc, lds_frag(&s_q[r16 * QRS + 32 * ks + 8 * q4]), kf[hh][ks]);
+      for (int ks = 0; ks < KS; ++ks) mma(acc, lds_frag(&s_q[query_of(r16) * QRS + 32 * ks + 8 * q4]), kf[hh][ks]);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) x[hh][i] = mul_nofuse(acc[i], c2);
+      for (int i = 0; i < NI; ++i) x[hh][i] = mul_nofuse(acc[i], c2);
     }
   }
 
   // One block at j0: x the base-2 logits (rows at or past t_end masked), vf the V
   // fragments of the same rows (dims 32 c + 8 (l / 16) + e).
-  __device__ __forceinline__ void block(const f32x4 (&x)[2], const FragT (&vf)[2][KS], int j0,
+  __device__ __forceinline__ void block(const float (&x)[2][NI], const FragT (&vf)[2][KS], int j0,
                                         int t_end, int G, int lane, VtTile& vt, PTile& sp) {
     const int r16 = lane & 15, q4 = lane >> 4, p2 = 2 * r16;
     wave_lds_order();  // the previous block's reads of vt / sp come first
@@ -283,12 +284,12 @@ struct EvAttn {
       }
     }
     // online softmax over the 32 rows
-    float alpha[4];
+    float alpha[NI];
     bool grew = false;
     const int ja = j0 + p2;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int g = 4 * q4 + i;
+    for (int i = 0; i < NI; ++i) {
+      const int g = 4 * i + q4;
       const bool gok = g < G;
       const float xa = (ja < t_end && gok) ? x[0][i] : -INFINITY;
       const float xb = (ja + 1 < t_end && gok) ? x[1][i] : -INFINITY;
@@ -305,25 +306,24 @@ struct EvAttn {
       grew |= mn != m_run[i];
       l_run[i] = l_run[i] * alpha[i] + row16_sum(pa + pb);
       m_run[i] = mn;
-      if (g < GM) {
-        if constexpr (sizeof(T) == 2) {
-          *reinterpret_cast<uint32_t*>(&sp[g][p2]) = bf16_pair(pa, pb);
-        } else {
-          sp[g][p2] = pa;
-          sp[g][p2 + 1] = pb;
-        }
+      if constexpr (sizeof(T) == 2) {
+        *reinterpret_cast<uint32_t*>(&sp[g][p2]) = bf16_pair(pa, pb);
+      } else {
+        sp[g][p2] = pa;
+        sp[g][p2 + 1] = pb;
       }
     }
     wave_lds_order();  // P and V are in LDS before they are read back
-    // O = alpha O + P . V (A = P rows g, B = V); alpha is exactly 1 where no running
+    // O = alpha O + P . V (A = the queries' rows of P, B = V); alpha is exactly 1 where no running
     // max grew, so the rescale is skipped when none did in the whole wave
     const bool rescale = __any(grew);
-    const FragT pfr = (r16 < G) ? load_frag(&sp[min(r16, GM - 1)][8 * q4]) : zero_frag<T>();
+    const int qr = query_of(r16);
+    const FragT pfr = (qr < G) ? load_frag(&sp[min(qr, GM - 1)][8 * q4]) : zero_frag<T>();
 #pragma unroll
     for (int nt = 0; nt < NOT; ++nt) {
       if (rescale) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) oacc[nt][i] *= alpha[i];
+        for (int i = 0; i < NI; ++i) oacc[nt][i] *= alpha[i];
       }
       if constexpr (TR)
         mma(oacc[nt], pfr, lds_frag_tr(&vt[0][0], LDV, 0, 16 * nt, lane));
@@ -338,18 +338,29 @@ struct EvAttn {
     else return p;
   }
 
-  // Running max of query 4 (l / 16) + (l % 4) (the same in the 16 lanes of a row).
+  // Running max of query 4 (l % NI) + l / 16 (the same in the 16 lanes of a row that share
+  // l % NI).
   __device__ __forceinline__ float m_of_lane(int lane) const {
-    const int i = lane & 3;
-    return i == 0 ? m_run[0] : (i == 1 ? m_run[1] : (i == 2 ? m_run[2] : m_run[3]));
+    // values, opaque: a select between elements of the array would become an indexed
+    // access, and the array would live in memory
+    float m[NI];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      m[i] = m_run[i];
+      asm volatile("" : "+v"(m[i]));
+    }
+    float r = m[0];
+#pragma unroll
+    for (int i = 1; i < NI; ++i) r = (lane & (NI - 1)) == i ? m[i] : r;
+    return r;
   }
 
   // o rows g < G to so[g * D + col], (max, sum) to ml[2 g].
   __device__ __forceinline__ void store_lds(float* so, float* ml, int G, int lane) const {
     const int r16 = lane & 15, q4 = lane >> 4;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int g = 4 * q4 + i;
+    for (int i = 0; i < NI; ++i) {
+      const int g = 4 * i + q4;
       if (g < G) {
 #pragma unroll
         for (int nt = 0; nt < NOT; ++nt) so[g * D + 16 * nt + r16] = oacc[nt][i];
@@ -730,7 +741,7 @@ __device__ __forceinline__ void select_finish(const EvictArgs& e, int head, int 
             vf2[hh][ks] = load_frag(vc + (size_t)j * D + 32 * ks + 8 * q4);
           }
         }
-        f32x4 xl[2];
+        float xl[2][EA::NI];
         EA::logits(s_q, kf2, c2, lane, xl);
         at.block(xl, vf2, j0, n, G, lane, vt[wave], sp[wave]);
       }
@@ -1019,14 +1030,14 @@ __device__ __forceinline__ void ev_segment(const EvictArgs& e, EvLds<T, D, GM, N
     EA at;
     at.init();
     auto process = [&](const FragT (&kf)[2][KS], const FragT (&vf)[2][KS], int j0) {
-      f32x4 x[2];
+      float x[2][EA::NI];
       EA::logits(L.q, kf, c2, lane, x);
       // scoring records; every lane stores (no branch around a store): a head that does
       // not evict writes into the first columns of the spare plane G + 1
       const int col = evicts ? j0 + 2 * r16 : 2 * r16;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int g = 4 * q4 + i;
+      for (int i = 0; i < EA::NI; ++i) {
+        const int g = 4 * i + q4;
         *reinterpret_cast<float2*>(&rec[(size_t)((evicts && g < G) ? g : G + 1) * ML + col]) =
             make_float2(x[0][i], x[1][i]);
       }
@@ -1082,8 +1093,8 @@ __device__ __forceinline__ void ev_segment(const EvictArgs& e, EvLds<T, D, GM, N
           make_float2(0.5f * log2f(rr[0]), 0.5f * log2f(rr[1]));  // the same from four lanes
       if constexpr (ATTN) {
         at.block(x, vf, j0, t1, G, lane, L.vt[wave], L.sp[wave]);
-        // the running max of query 4 (l / 16) + (l % 4) after this block
-        const int gm = 4 * q4 + (lane & 3);
+        // the running maxima after this block
+        const int gm = 4 * (lane & (EA::NI - 1)) + q4;
         bmr[((evicts && gm < G) ? gm : G) * NB + (evicts ? j0 / kEvTB : 0)] = at.m_of_lane(lane);
       }
     };

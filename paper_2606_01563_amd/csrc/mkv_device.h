@@ -195,6 +195,13 @@ __device__ __forceinline__ int wave_incl_scan(int x) {
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// ---------------------------------------------------------------- query rows
+// Query g of a group sits in MFMA row (column) 4 (g % 4) + g / 4, so that a lane's result
+// rows 4 (l / 16) + i hold queries 4 i + l / 16: with up to four queries per group only
+// i = 0 is work (the online softmax of four rows per lane, three of them padding, was most
+// of a block's vector instructions), with up to eight i = 0, 1.  The map is its own inverse.
+__device__ __forceinline__ int query_of(int row) { return 4 * (row & 3) + (row >> 2); }
+
 // ---------------------------------------------------------------- in-launch hand-off
 // Results that one workgroup hands to another of the same launch go through agent-scope
 // relaxed atomic stores and loads, which are not served from the per-XCD caches.  A writer
