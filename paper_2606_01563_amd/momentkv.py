@@ -9,6 +9,7 @@ kernels.  The library is loaded on first use; a missing library raises.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 import re
 from dataclasses import dataclass
@@ -195,8 +196,46 @@ def _check_workspace(ws, name: str = "workspace"):
         raise ValueError(f"{name} must be a 1-D torch.uint8 tensor")
 
 
+# The handle of the current stream without building a Stream object (about 4 us per call).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
+
+
+def _pointers(required, optional) -> list | None:
+    """Data pointers of (tensor, shape, dtype) entries, the optional ones None where the
+    tensor is: one pass over what _expect and _same_device check (every tensor a contiguous
+    GPU tensor of exactly this shape and dtype, all on one device).  None if any entry is
+    not: the caller then runs those checks, which say what is wrong.  Every call checks its
+    own tensors; a token is 36 such calls and more, and apart the checks took longer than a
+    short launch."""
+    ptrs, dev = [], None
+    for entries in (required, optional):
+        for t, shape, dt in entries:
+            if t is None and entries is optional:
+                ptrs.append(None)
+                continue
+            if not isinstance(t, torch.Tensor) or t.dtype is not dt or t.shape != shape:
+                return None
+            i = t.get_device()
+            if i < 0 or (dev is not None and i != dev) or not t.is_contiguous():
+                return None
+            dev = i
+            ptrs.append(t.data_ptr())
+    return ptrs
+
+
+@functools.lru_cache(maxsize=512, typed=True)
+def _decode_plan(*fields):
+    """The parameter block of these values (read only: shared by the calls that have them),
+    and its workspace sizes: decode, its zero prefix, eviction."""
+    p = DecodeParams(*fields)
+    return (p, momentkv_decode_workspace_bytes(p), momentkv_decode_workspace_zero_bytes(p),
+            momentkv_decode_evict_workspace_bytes(p))
 
 
 def _workspace(nbytes: int, device, ws: torch.Tensor | None) -> torch.Tensor:
@@ -418,6 +457,44 @@ def _check_decode_args(q, k_cache, v_cache, lens, n_e, s_k, s_v, S, k_new, v_new
                       evicted=evicted, workspace=workspace))
 
 
+def _decode_pointers(q, k_cache, v_cache, lens, n_e, s_k, s_v, S, k_new, v_new, out, lse, w_r,
+                     workspace, summary, evicted=None, need_new=False) -> list:
+    """Pointers of q, k_cache, v_cache, lens, n_e, s_k, s_v, S, k_new, v_new, out, lse, w_r,
+    evicted after the checks of _check_decode_args (which it runs, to raise, when the quick
+    pass does not accept the arguments)."""
+    ptrs = None
+    if isinstance(q, torch.Tensor) and isinstance(k_cache, torch.Tensor) and q.dim() == 3 \
+            and k_cache.dim() == 4 and (k_new is None) == (v_new is None) \
+            and not (need_new and k_new is None):
+        dt, f32, i32 = q.dtype, torch.float32, torch.int32
+        B, Hq, d = q.shape
+        _, Hkv, cap, _ = k_cache.shape
+        cache, head, vec = (B, Hkv, cap, d), (B, Hkv), (B, Hkv, d)
+        mat, S_dt = (B, Hkv, d, d), f32
+        known = dt is f32 or dt is torch.bfloat16
+        if summary == 1 and dt is torch.bfloat16:
+            mat, S_dt = (B, Hkv, 2, d, d), dt
+        elif summary == 2 or summary == 3:
+            S_dt = torch.bfloat16
+        elif summary != 0 and summary != 1:
+            known = False
+        if known:
+            opt = [(k_new, vec, dt), (v_new, vec, dt), (out, (B, Hq, d), dt), (lse, (B, Hq), f32),
+                   (w_r, (B, Hq), f32), (evicted, head, i32)]
+            if isinstance(workspace, torch.Tensor):
+                opt.append((workspace, (workspace.numel(),), torch.uint8))
+            if workspace is None or isinstance(workspace, torch.Tensor):
+                ptrs = _pointers(((q, (B, Hq, d), dt), (k_cache, cache, dt), (v_cache, cache, dt),
+                                  (lens, head, i32), (n_e, head, i32), (s_k, vec, f32),
+                                  (s_v, vec, f32), (S, mat, S_dt)), opt)
+    if ptrs is None:
+        _check_decode_args(q, k_cache, v_cache, lens, n_e, s_k, s_v, S, k_new, v_new, out, lse,
+                           w_r, workspace, summary, evicted=evicted, need_new=need_new)
+        ptrs = [_ptr(t) for t in (q, k_cache, v_cache, lens, n_e, s_k, s_v, S, k_new, v_new, out,
+                                  lse, w_r, evicted)]
+    return ptrs
+
+
 def momentkv_decode_attn(q: torch.Tensor, k_cache: torch.Tensor, v_cache: torch.Tensor,
                          lens: torch.Tensor, n_e: torch.Tensor, s_k: torch.Tensor,
                          s_v: torch.Tensor, S: torch.Tensor, *, k_new: torch.Tensor | None = None,
@@ -438,24 +515,22 @@ def momentkv_decode_attn(q: torch.Tensor, k_cache: torch.Tensor, v_cache: torch.
     counters) are zeroed here the first time a workspace tensor is used with this prefix
     length (the flag included); calls leave the counters at zero.
     """
-    _check_decode_args(q, k_cache, v_cache, lens, n_e, s_k, s_v, S, k_new, v_new, out, lse, w_r,
-                       workspace, summary)
-    cap = k_cache.shape[2]
-    p = decode_params(q, k_cache, max_len=cap if max_len is None else max_len, order=order,
-                      scale=scale, tau=tau, n_split=n_split, summary=summary)
-    dev = q.device
+    ptr = _decode_pointers(q, k_cache, v_cache, lens, n_e, s_k, s_v, S, k_new, v_new, out, lse,
+                           w_r, workspace, summary)
+    B, Hq, d = q.shape
+    _, Hkv, cap, _ = k_cache.shape
+    p, nbytes, zero, _ = _decode_plan(B, Hq, Hkv, d, cap, cap if max_len is None else max_len, order,
+                                      _dtype_code(q), scale, tau, n_split, summary)
     if out is None:
         out = torch.empty_like(q)
-    nbytes = momentkv_decode_workspace_bytes(p)
+        ptr[10] = out.data_ptr()
     if nbytes == 0:
         code = lib().momentkv_decode_attn(ctypes.byref(p), *([None] * 13), None, 0, None)
         raise MomentKVError(code, "momentkv_decode_attn")
-    ws = _workspace(nbytes, dev, workspace)
-    _zero_prefix(ws, momentkv_decode_workspace_zero_bytes(p))
-    code = lib().momentkv_decode_attn(
-        ctypes.byref(p), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(lens), _ptr(k_new),
-        _ptr(v_new), _ptr(n_e), _ptr(s_k), _ptr(s_v), _ptr(S), _ptr(out), _ptr(lse), _ptr(w_r),
-        ws.data_ptr(), ws.numel(), _stream())
+    ws = _workspace(nbytes, q.device, workspace)
+    _zero_prefix(ws, zero)
+    code = lib().momentkv_decode_attn(ctypes.byref(p), *ptr[:4], ptr[8], ptr[9], *ptr[4:8],
+                                      *ptr[10:13], ws.data_ptr(), ws.numel(), _stream())
     if code != 0:
         raise MomentKVError(code, "momentkv_decode_attn")
     return out, lse, w_r, ws
@@ -474,17 +549,16 @@ def momentkv_decode_attn_noalloc(q: torch.Tensor, k_cache: torch.Tensor, v_cache
     the partial results in its own per-GPU device array.  Every buffer, `out` included, is
     the caller's, so nothing is allocated here either.  `flag`: None or a one-element int32
     tensor that the call sets to 1 when an append finds a full cache.  Returns out."""
-    _check_decode_args(q, k_cache, v_cache, lens, n_e, s_k, s_v, S, k_new, v_new, out, lse, w_r,
-                       None, summary)
+    ptr = _decode_pointers(q, k_cache, v_cache, lens, n_e, s_k, s_v, S, k_new, v_new, out, lse,
+                           w_r, None, summary)
     _expect(flag, "flag", (1,), torch.int32, optional=True)
     _same_device(dict(q=q, flag=flag))
-    cap = k_cache.shape[2]
-    p = decode_params(q, k_cache, max_len=cap if max_len is None else max_len, order=order,
-                      scale=scale, tau=tau, n_split=n_split, summary=summary)
-    code = lib().momentkv_decode_attn_noalloc(
-        ctypes.byref(p), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(lens), _ptr(k_new),
-        _ptr(v_new), _ptr(n_e), _ptr(s_k), _ptr(s_v), _ptr(S), _ptr(out), _ptr(lse), _ptr(w_r),
-        _ptr(flag), _stream())
+    B, Hq, d = q.shape
+    _, Hkv, cap, _ = k_cache.shape
+    p = _decode_plan(B, Hq, Hkv, d, cap, cap if max_len is None else max_len, order, _dtype_code(q),
+                     scale, tau, n_split, summary)[0]
+    code = lib().momentkv_decode_attn_noalloc(ctypes.byref(p), *ptr[:4], ptr[8], ptr[9], *ptr[4:8],
+                                              *ptr[10:13], _ptr(flag), _stream())
     if code != 0:
         raise MomentKVError(code, "momentkv_decode_attn_noalloc")
     return out
@@ -502,27 +576,25 @@ def momentkv_decode_evict(q: torch.Tensor, k_cache: torch.Tensor, v_cache: torch
     """Decode step with moment-informed eviction (see the header).  The caches, lens and
     the raw summary (n_e, s_k, s_v, S) are updated in place.
     Returns (out, lse, w_r, evicted, workspace)."""
-    _check_decode_args(q, k_cache, v_cache, lens, n_e, s_k, s_v, S, k_new, v_new, out, lse, w_r,
-                       workspace, 0, evicted=evicted, need_new=True)
-    cap = k_cache.shape[2]
-    p = decode_params(q, k_cache, max_len=cap if max_len is None else max_len, order=order,
-                      scale=scale, tau=tau, n_split=n_split, summary=0)
-    dev = q.device
+    ptr = _decode_pointers(q, k_cache, v_cache, lens, n_e, s_k, s_v, S, k_new, v_new, out, lse,
+                           w_r, workspace, 0, evicted=evicted, need_new=True)
+    B, Hq, d = q.shape
+    _, Hkv, cap, _ = k_cache.shape
+    p, _, _, nbytes = _decode_plan(B, Hq, Hkv, d, cap, cap if max_len is None else max_len, order,
+                                   _dtype_code(q), scale, tau, n_split, 0)
     if out is None:
         out = torch.empty_like(q)
-    nbytes = momentkv_decode_evict_workspace_bytes(p)
+        ptr[10] = out.data_ptr()
     if nbytes == 0:
         code = lib().momentkv_decode_evict(ctypes.byref(p), int(budget), *([None] * 14), None,
                                            0, None)
         raise MomentKVError(code, "momentkv_decode_evict")
     fresh = workspace is None or workspace.numel() < nbytes
-    ws = _workspace(nbytes, dev, workspace)
+    ws = _workspace(nbytes, q.device, workspace)
     if fresh:
         ws[:256].zero_()  # the sticky flag
-    code = lib().momentkv_decode_evict(
-        ctypes.byref(p), int(budget), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(lens),
-        _ptr(k_new), _ptr(v_new), _ptr(n_e), _ptr(s_k), _ptr(s_v), _ptr(S), _ptr(out),
-        _ptr(lse), _ptr(w_r), _ptr(evicted), ws.data_ptr(), ws.numel(), _stream())
+    code = lib().momentkv_decode_evict(ctypes.byref(p), int(budget), *ptr[:4], ptr[8], ptr[9],
+                                       *ptr[4:8], *ptr[10:14], ws.data_ptr(), ws.numel(), _stream())
     if code != 0:
         raise MomentKVError(code, "momentkv_decode_evict")
     return out, lse, w_r, evicted, ws

@@ -332,3 +332,12 @@ def test_noalloc_decode_rejects_requests_beyond_its_scratch_before_any_device_ca
     assert L.momentkv_decode_attn_noalloc(ctypes.byref(dparams(head_dim=96)), *ptrs, None,
                                           None) == UNSUP
     assert L.momentkv_decode_attn_noalloc(None, *ptrs, None, None) == NULL
+
+
+def test_decode_plan_of_equal_values_of_other_types_is_refused():
+    """The parameter blocks kept per value tell 128 from 128.0: what ctypes refuses stays
+    refused after a call with the equal integer."""
+    ok = (1, 4, 1, 64, 128, 128, 1, 1, 0.0, 1e-6, 0, 0)
+    assert mk._decode_plan(*ok)[1] > 0
+    with pytest.raises(TypeError):
+        mk._decode_plan(*ok[:5], 128.0, *ok[6:])
