@@ -50,6 +50,7 @@ namespace {
 constexpr int kEvTB = 32;           // rows per block
 constexpr int kFinWaves = 4;        // waves of a finishing workgroup
 constexpr int kMaxSlices = 64;      // partial states merged by one finishing wave
+constexpr int kShortRows = 320;     // rows of a head in the short-cache launch, at most
 constexpr float kRedoRatio = 16.f;  // recompute when a removed term exceeds this many
                                     // times what remains of a query's sum
 
@@ -440,16 +441,20 @@ __device__ __forceinline__ int s_at(int row, int col) {
 // held in registers only from there on.
 // pre(qs) runs once those first requests are out (the finishing launch combines the
 // partial states there).
-template <class T, int D, int GM, int NW, int RW, bool ATTN, class Pre>
+// Without ATTN, sl.m and sl.l hold the scoring waves' (max, sum) of the base-2 logits per
+// query.  LREC: the records are in LDS at lrec, [GM + 1][kShortRows], the norms last.
+template <class T, int D, int GM, int NW, int RW, bool ATTN, bool LREC, class Pre>
 __device__ __forceinline__ void select_finish(const EvictArgs& e, int head, int old_len, QState<GM, NW, D>& qs,
                               SelLds<GM, NW, D>& sl, typename EvAttn<T, D, GM>::VtTile* vt,
                               typename EvAttn<T, D, GM>::PTile* sp, float* ml, const T* s_q,
-                              float* s_S, Pre&& pre) {
+                              float* s_S, const float* lrec, Pre&& pre) {
   typedef EvAttn<T, D, GM> EA;
   typedef typename EA::FragT FragT;
   constexpr int NT = NW * kWave, KS = D / 32, CPL = D / 64, QRS = EA::QRS;
   constexpr int KQ = QState<GM, NW, D>::KQ;
-  constexpr int UB = GM <= 4 ? 16 : (GM <= 8 ? 8 : 4);  // records per thread per batch
+  // records per thread per batch
+  constexpr int UB = LREC ? 4 : (GM <= 4 ? 16 : (GM <= 8 ? 8 : 4));
+  static_assert(!LREC || UB * NT >= kShortRows, "one batch");
   constexpr int SPER = D * D / 4 / NT;                 // float4 entries of S per thread
   constexpr int SCH = SPER < 16 ? SPER : 16;           // of which in registers at a time
   constexpr int NCH = SPER / SCH;
@@ -459,9 +464,9 @@ __device__ __forceinline__ void select_finish(const EvictArgs& e, int head, int 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool can_append = old_len >= 0 && old_len < e.cap;
   const bool evicts = head_evicts(e, old_len);
-  const int G = e.G, ML = e.rec_len, NB = e.rec_len / kEvTB;
+  const int G = e.G, ML = LREC ? kShortRows : e.rec_len, NB = e.rec_len / kEvTB;
   const int n_tok = old_len + 1, last = n_tok - 1;
-  const float* rec = e.rec + (size_t)head * (G + 2) * ML;
+  const float* rec = LREC ? lrec : e.rec + (size_t)head * (G + 2) * ML;
   T* kc = reinterpret_cast<T*>(e.k_cache) + (size_t)head * e.cap * D;
   T* vc = reinterpret_cast<T*>(e.v_cache) + (size_t)head * e.cap * D;
   float4* Sh = reinterpret_cast<float4*>(e.S + (size_t)head * D * D);
@@ -498,7 +503,7 @@ __device__ __forceinline__ void select_finish(const EvictArgs& e, int head, int 
       const int jc = min(base + 4 * (tid + NT * v), ML - 4);  // past the planes: rows past n_tok
 #pragma unroll
       for (int g = 0; g <= GM; ++g)
-        r4[v][g] = *reinterpret_cast<const float4*>(rec + (size_t)(g < GM ? min(g, G - 1) : G) * ML + jc);
+        r4[v][g] = *reinterpret_cast<const float4*>(rec + (size_t)(g < GM ? min(g, G - 1) : (LREC ? GM : G)) * ML + jc);
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -536,38 +541,7 @@ __device__ __forceinline__ void select_finish(const EvictArgs& e, int head, int 
       }
       __syncthreads();
     } else {
-      // log2 Z_g over the n_tok rows: per batch the thread's max, then its sum (records past
-      // n_tok and padded query slots hold -inf and add nothing; no per-record branch)
-      float m[GM], l[GM];
-#pragma unroll
-      for (int g = 0; g < GM; ++g) { m[g] = -INFINITY; l[g] = 0.f; }
-      for (int b = 0; b < nb; ++b) {
-        if (b > 0) load_batch(b * step);
-        const int nv = groups_in(b * step);
-#pragma unroll
-        for (int g = 0; g < GM; ++g) {
-          float mn = m[g];
-#pragma unroll
-          for (int u = 0; u < UB; ++u)
-            if (u / 4 < nv) mn = fmaxf(mn, x[u][g]);
-          const float base = mn == -INFINITY ? 0.f : mn;
-          float sum = 0.f;
-#pragma unroll
-          for (int u = 0; u < UB; ++u)
-            if (u / 4 < nv) sum += fast_exp2(x[u][g] - base);
-          l[g] = l[g] * fast_exp2(m[g] - base) + sum;
-          m[g] = mn;
-        }
-      }
-#pragma unroll
-      for (int g = 0; g < GM; ++g) {
-        if (g < G) {
-          const float M = wave_max(m[g]);
-          const float ls = wave_sum(M == -INFINITY ? 0.f : l[g] * fast_exp2(m[g] - M));
-          if (lane == 0) { sl.m[wave][g] = M; sl.l[wave][g] = ls; }
-        }
-      }
-      __syncthreads();
+      // log2 Z_g from the scoring waves' sums
       if (tid < G) {
         float M = -INFINITY, L = 0.f;
 #pragma unroll
@@ -614,12 +588,10 @@ __device__ __forceinline__ void select_finish(const EvictArgs& e, int head, int 
         bj = better ? j : bj;
       }
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      const float ob = __shfl_xor(best, off);
-      const int oj = __shfl_xor(bj, off);
-      if (ob < best || (ob == best && oj < bj)) { best = ob; bj = oj; }
-    }
+    // the lowest score of the wave (never NaN), then the lowest row that has it
+    const float wave_best = wave_min(best);
+    bj = wave_min_i(best == wave_best ? bj : INT_MAX);
+    best = wave_best;
     if (lane == 0) { sl.best[wave] = best; sl.bj[wave] = bj; }
     __syncthreads();
     if (tid == 0) {
@@ -913,12 +885,24 @@ template <class T, int D, int GM, int NW> struct EvLds<T, D, GM, NW, true> {
   float vinit[D];             // s_v / scale: the start of the S_tilde k accumulators
   float ml[NW * 2 * GM];
 };
-template <class T, int D, int GM, int NW> struct EvLds<T, D, GM, NW, false> {
+template <class T, int D, int GM, int NW> struct EvShortLds {
   typedef EvAttn<T, D, GM> EA;
   SumLds<T, D> sm;
   T q[16 * EA::QRS];
   float vinit[D];             // s_v / scale: the start of the S_tilde k accumulators
   SelLds<GM, NW, D> sel;
+};
+// The short-cache launch keeps its score records in LDS where two workgroups still fit a CU
+// (in memory, writing them, waiting until they are visible and reading them back, and a
+// pass over them for log2 Z, which the scoring waves now sum as they go, took 4 of 33 us
+// for 288 heads of 128 rows).
+template <class T, int D, int GM, int NW>
+constexpr bool ev_lrec() {
+  return sizeof(EvShortLds<T, D, GM, NW>) + (GM + 1) * kShortRows * sizeof(float) <= 80 * 1024;
+}
+template <class T, int D, int GM, int NW>
+struct EvLds<T, D, GM, NW, false> : EvShortLds<T, D, GM, NW> {
+  __align__(16) float rec[ev_lrec<T, D, GM, NW>() ? (GM + 1) * kShortRows : 4];
 };
 
 template <class T, int D, int GM>
@@ -957,6 +941,7 @@ __device__ __forceinline__ void ev_segment(const EvictArgs& e, EvLds<T, D, GM, N
   constexpr int NTI = D / 16;  // 16-row tiles of S_tilde k
   constexpr int NT = NW * kWave;
   constexpr int CPL = D / 64;
+  constexpr bool LREC = !ATTN && ev_lrec<T, D, GM, NW>();
   // the wave index, lengths and loop bounds are the same for all lanes; held in scalar
   // registers, they make the loops below uniform control flow rather than per-lane loops
   const int tid = tid_here();
@@ -1029,6 +1014,9 @@ __device__ __forceinline__ void ev_segment(const EvictArgs& e, EvLds<T, D, GM, N
 
     EA at;
     at.init();
+    float zm[EA::NI], zl[EA::NI];  // scoring alone: the lane's (max, sum) of the logits
+#pragma unroll
+    for (int i = 0; i < EA::NI; ++i) { zm[i] = -INFINITY; zl[i] = 0.f; }
     auto process = [&](const FragT (&kf)[2][KS], const FragT (&vf)[2][KS], int j0) {
       float x[2][EA::NI];
       EA::logits(L.q, kf, c2, lane, x);
@@ -1038,8 +1026,23 @@ __device__ __forceinline__ void ev_segment(const EvictArgs& e, EvLds<T, D, GM, N
 #pragma unroll
       for (int i = 0; i < EA::NI; ++i) {
         const int g = 4 * i + q4;
-        *reinterpret_cast<float2*>(&rec[(size_t)((evicts && g < G) ? g : G + 1) * ML + col]) =
-            make_float2(x[0][i], x[1][i]);
+        if constexpr (LREC) {  // (the launch scores only heads that evict)
+          if (g < G) *reinterpret_cast<float2*>(&L.rec[g * kShortRows + col]) = make_float2(x[0][i], x[1][i]);
+        } else {
+          *reinterpret_cast<float2*>(&rec[(size_t)((evicts && g < G) ? g : G + 1) * ML + col]) =
+              make_float2(x[0][i], x[1][i]);
+        }
+      }
+      if constexpr (!ATTN) {  // the lane's share of log2 Z, rows past the end left out
+#pragma unroll
+        for (int i = 0; i < EA::NI; ++i) {
+          const float xa = j0 + 2 * r16 < t1 ? x[0][i] : -INFINITY;
+          const float xb = j0 + 2 * r16 + 1 < t1 ? x[1][i] : -INFINITY;
+          const float mn = fmaxf(zm[i], fmaxf(xa, xb));
+          const float ms = mn == -INFINITY ? 0.f : mn;
+          zl[i] = zl[i] * fast_exp2(zm[i] - ms) + (fast_exp2(xa - ms) + fast_exp2(xb - ms));
+          zm[i] = mn;
+        }
       }
       float rr[2] = {1.f, 1.f};
       if (evicts) {
@@ -1089,8 +1092,10 @@ __device__ __forceinline__ void ev_segment(const EvictArgs& e, EvLds<T, D, GM, N
         rr[0] = cross_row_sum(rr[0]);
         rr[1] = cross_row_sum(rr[1]);
       }
-      *reinterpret_cast<float2*>(&rec[(size_t)(evicts ? G : G + 1) * ML + col]) =
-          make_float2(0.5f * log2f(rr[0]), 0.5f * log2f(rr[1]));  // the same from four lanes
+      const float2 y2 = make_float2(0.5f * log2f(rr[0]), 0.5f * log2f(rr[1]));
+      // the same from four lanes
+      if constexpr (LREC) *reinterpret_cast<float2*>(&L.rec[GM * kShortRows + col]) = y2;
+      else *reinterpret_cast<float2*>(&rec[(size_t)(evicts ? G : G + 1) * ML + col]) = y2;
       if constexpr (ATTN) {
         at.block(x, vf, j0, t1, G, lane, L.vt[wave], L.sp[wave]);
         // the running maxima after this block
@@ -1109,6 +1114,18 @@ __device__ __forceinline__ void ev_segment(const EvictArgs& e, EvLds<T, D, GM, N
       process(kb, vb, j0 + NW * kEvTB);
     }
 
+    if constexpr (!ATTN) {
+#pragma unroll
+      for (int i = 0; i < EA::NI; ++i) {
+        const float M = row16_max(zm[i]);
+        const float l = row16_sum(M == -INFINITY ? 0.f : zl[i] * fast_exp2(zm[i] - M));
+        const int g = 4 * i + q4;
+        if (r16 == 0 && g < G) {
+          L.sel.m[wave][g] = M;
+          L.sel.l[wave][g] = l;
+        }
+      }
+    }
     if constexpr (ATTN) {
       // the waves' states, merged per query, as the head's partial `slot`
       wave_lds_order();
@@ -1158,9 +1175,9 @@ __device__ __forceinline__ void ev_segment(const EvictArgs& e, EvLds<T, D, GM, N
     }
     __syncthreads();
     QState<GM, NW, D> qs;
-    select_finish<T, D, GM, NW, RW, false>(e, head, old_len, qs, L.sel, vt, sp, ml, L.q,
-                                           reinterpret_cast<float*>(&L.sm),
-                                           [](QState<GM, NW, D>&) {});
+    select_finish<T, D, GM, NW, RW, false, LREC>(e, head, old_len, qs, L.sel, vt, sp, ml, L.q,
+                                                 reinterpret_cast<float*>(&L.sm), L.rec,
+                                                 [](QState<GM, NW, D>&) {});
   }
 }
 
@@ -1258,8 +1275,9 @@ __global__ void __launch_bounds__(kFinWaves * kWave, 2) k_evict_finish(EvictArgs
     qr.store(L.q);  // read after the selection's barriers
   };
   QState<GM, kFinWaves, D> qs;
-  select_finish<T, D, GM, kFinWaves, kFinWaves, true>(e, head, old_len, qs, L.sel, L.u.r.vt,
-                                                      L.u.r.sp, L.ml, L.q, L.u.S, combine);
+  select_finish<T, D, GM, kFinWaves, kFinWaves, true, false>(e, head, old_len, qs, L.sel, L.u.r.vt,
+                                                             L.u.r.sp, L.ml, L.q, L.u.S, nullptr,
+                                                             combine);
 }
 
 int evict_waves(bool bf16, int G) {
@@ -1291,6 +1309,7 @@ static hipError_t launch_evict_t(const EvictArgs& e, hipStream_t st) {
 
 hipError_t launch_evict(const EvictArgs& e, bool bf16, int d, hipStream_t st) {
   if (e.fused && (e.nwg < 1 || e.maxslots < 1 || e.maxslots > kMaxSlices)) return hipErrorInvalidValue;
+  if (!e.fused && e.rec_len > kShortRows) return hipErrorInvalidValue;
   if (bf16) return d == 64 ? launch_evict_t<bf16_t, 64>(e, st) : launch_evict_t<bf16_t, 128>(e, st);
   return d == 64 ? launch_evict_t<float, 64>(e, st) : launch_evict_t<float, 128>(e, st);
 }

@@ -178,6 +178,24 @@ __device__ __forceinline__ float cross_row_max(float x) {
 __device__ __forceinline__ float wave_sum(float x) { return cross_row_sum(row16_sum(x)); }
 __device__ __forceinline__ float wave_max(float x) { return cross_row_max(row16_max(x)); }
 
+__device__ __forceinline__ float wave_min(float x) {
+  x = fminf(x, dpp_f<0x128>(x));
+  x = fminf(x, dpp_f<0x124>(x));
+  x = fminf(x, dpp_f<0x122>(x));
+  x = fminf(x, dpp_f<0x121>(x));
+  return cross_row(x, [](float p, float q) { return fminf(p, q); });
+}
+__device__ __forceinline__ int wave_min_i(int x) {
+  x = min(x, dpp_i<0x128>(x));
+  x = min(x, dpp_i<0x124>(x));
+  x = min(x, dpp_i<0x122>(x));
+  x = min(x, dpp_i<0x121>(x));
+  const auto r = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)x, false, false);
+  x = min((int)r[0], (int)r[1]);
+  const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)x, false, false);
+  return min((int)h[0], (int)h[1]);
+}
+
 // Inclusive prefix sum over the 64 lanes through DPP (row shifts, then the row totals
 // broadcast into the rows after): no LDS round trips.
 template <int CTRL, int ROWS> __device__ __forceinline__ int dpp_rows_i(int x) {
