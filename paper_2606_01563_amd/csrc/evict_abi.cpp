@@ -17,7 +17,7 @@ using namespace mkv::abi;
 namespace {
 
 // ------------------------------------------------------------------ decode + eviction
-// Two launch shapes.  Fused (one read of the cache; from kFusedMinLen rows, or whenever
+// Two launch shapes.  Fused (one read of the cache; from fused_min_len() rows, or whenever
 // n_split > 0): the scoring launch has one workgroup per CU of the target (kCUs; n_split
 // per head when n_split > 0), each taking an equal contiguous share of the flattened
 // (head, 32-row block) range, so that a head has at most maxslots partial states (at most
@@ -29,9 +29,25 @@ namespace {
 // Workspace: the flag first, then the score records and the per-block running maxima;
 // fused: then the heads' partial states.
 constexpr int kCUs = 256;
-// max_len from which the one-read shape runs (on a 288-head stack it was the faster one
-// from 384 rows up and the slower one at 256)
-constexpr int kFusedMinLen = 320;
+// max_len from which the one-read shape runs.  Measured per call (d = 128, G = 4), short
+// against one-read shape, us:
+//   bf16   8 heads    200 rows 21.8 / 20.4   300 rows 25.7 / 20.6
+//          32 heads   200 rows 22.0 / 23.7   300 rows 26.0 / 23.9
+//          64 heads   200 rows 22.4 / 25.4   300 rows 26.4 / 25.4
+//          288 heads  200 rows 33.1 / 38.9   300 rows 41.2 / 42.6
+//   fp32   8 heads     64 rows 31.1 / 29.0   128 rows 46.8 / 29.2
+//          64 heads    64 rows 31.8 / 34.1   128 rows 49.4 / 34.8
+//          288 heads   64 rows 52.8 / 59.3   128 rows 75.1 / 72.1   300 rows 124 / 87
+// (few heads leave CUs idle that the one-read shape shares out; in fp32 a block's products
+// take the one workgroup of a head several times as long, and it has the registers for few
+// waves).
+constexpr int kFusedMinLen = 320, kFusedMinLenFew = 256, kFusedMinLenF32 = 112;
+constexpr int kFewHeads = 64;
+
+int fused_min_len(const mkv_decode_params* p) {
+  if (p->dtype == MKV_F32) return kFusedMinLenF32;
+  return (int64_t)p->batch * p->n_kv_heads <= kFewHeads ? kFusedMinLenFew : kFusedMinLen;
+}
 
 mkv::EvictArgs evict_layout(const mkv_decode_params* p, int32_t budget, void* ws, size_t* total) {
   mkv::EvictArgs e;
@@ -46,7 +62,7 @@ mkv::EvictArgs evict_layout(const mkv_decode_params* p, int32_t budget, void* ws
   e.tau = p->tau;
   e.hblocks = ceil_div(p->max_len, 32);
   e.rec_len = 32 * e.hblocks;
-  e.fused = (p->n_split > 0 || p->max_len >= kFusedMinLen) ? 1 : 0;
+  e.fused = (p->n_split > 0 || p->max_len >= fused_min_len(p)) ? 1 : 0;
   const size_t H = e.n_heads, G = e.G, D = p->head_dim;
   Carver c;
   c.base = static_cast<char*>(ws);

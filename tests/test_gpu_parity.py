@@ -713,6 +713,19 @@ def test_evict_at_the_launch_shape_bound(budget):
     assert n == 3 * 2
 
 
+@pytest.mark.parametrize("dtype,budget", [(torch.bfloat16, 254), (torch.bfloat16, 255),
+                                          (torch.float32, 110), (torch.float32, 111)])
+def test_evict_at_the_bounds_for_few_heads_and_fp32(dtype, budget):
+    """Both sides of the row bounds between the launch shapes (max_len 256 with few heads,
+    112 in fp32)."""
+    wl, cpu, gpu = layer("tiny_fp32_n2048", steps=4, dtype=dtype, head_dim=128, ctx_len=1000,
+                         batch=2, n_q_heads=8, n_kv_heads=2, window=16, budgets=(budget,))
+    out = P.run_compress(gpu, budget, cap=budget + 1)
+    worst, swaps, n_ev = P.run_evict_steps(gpu, out, 4, budget)
+    assert n_ev == 4 * 2 * 2
+    announce(f"{dtype} budget {budget}: worst {worst:.2e}, near-tie swaps {swaps}")
+
+
 @pytest.mark.parametrize("n_split,ctx", [(0, 300), (0, 700), (1, 700)])
 def test_evict_with_empty_summary_scores_alpha_times_value_norm(n_split, ctx):
     """Budget above the context keeps every token, so n_e = 0: the first evictions use
