@@ -28,16 +28,26 @@ constexpr int64_t kMaxDecodeWaves = 1 << 24;  // decode grid limit (single-wave 
 //   128 heads  512 rows 13.4 / 16.6 / 16.4   1024 rows 20.5 / 21.3 / 21.4
 //   256 heads  512 rows 17.3 / 21.0 / 22.5   1024 rows 26.7 / 29.9 / 35.8
 //   288 heads  384 rows 21.2 / 20.7 / 25.4    512 rows 25.7 / 24.1 / 30.0
+// and with lengths spread over a quarter to all of max_len (one workgroup / slices / groups):
+//   48 heads  1020 rows 19.6 / 14.7 / 12.2   1500 rows   -  / 14.7 / 13.8
+//   64 heads  1020 rows 19.0 / 13.8 / 13.5   1500 rows   -  / 14.8 / 15.9
+//   96 heads   450 rows 12.1 / 13.1 / 15.4   1020 rows 19.5 / 15.0 / 19.2
+//   128 heads  600 rows 14.2 / 15.8 / 18.2   1020 rows 19.6 / 17.0 / 20.0
+//   192 heads  600 rows 14.4 / 17.3 / 23.6   1020 rows 19.7 / 19.9 / 31.1
 // Up to 256 rows every head runs in one workgroup.  Longer caches of few heads: the
-// smallest group length (a multiple of 128 rows, to 768) that keeps the launch at kGroupWgs
-// token workgroups, so that with the heads' S_tilde q workgroups each starts at once on a
-// CU of its own.  Heads that fill the CUs at most once and caches that are short enough:
-// one workgroup per head, which needs no hand-off.  Else slices.
-constexpr int kFusedMaxLen = 256;
-constexpr int kFusedMaxLenMany = 384;
-constexpr int kFusedMaxLenFull = 1024;  // up to kCUs heads
+// smallest group length (a multiple of 128 rows) that keeps the launch at kGroupWgs token
+// workgroups and, from 8 waves each (one workgroup per CU), with the heads' S_tilde q
+// workgroups at the CUs, so that each starts at once; longer groups than kGroupMaxLen lose
+// to slices where the lengths differ, except with so few heads that slices are many per
+// head.  Otherwise one workgroup per head, which needs no hand-off, while the caches are
+// short for how far the heads fill the CUs; else slices.
 constexpr int kCUs = 256;
-constexpr int kGroupWgs = 192, kGroupMaxLen = 768;
+constexpr int kFusedMaxLen = 256;
+constexpr int kFusedMaxLenMany = 384;   // any number of heads
+constexpr int kFusedMaxLenHalf = 640;   // up to kCUs / 2 heads
+constexpr int kFusedMaxLenFull = 1024;  // kCUs / 2 to kCUs heads
+constexpr int kGroupWgs = 192, kGroupMaxLen = 384;
+constexpr int kGroupVeryFewHeads = 32, kGroupMaxLenVeryFew = 768;
 
 // ----------------------------------------------------------------------- decode
 // Token slices per KV head.  Slices shape with n_split = 0: about kDecodeWaves single-wave
@@ -47,9 +57,11 @@ constexpr int kGroupWgs = 192, kGroupMaxLen = 768;
 mkv::DecodeShape decode_shape(const mkv_decode_params* p, int* split_len, int* nsplit) {
   const int64_t heads = (int64_t)p->batch * p->n_kv_heads;
   if (p->n_split == 0 && p->max_len > kFusedMaxLen) {
-    for (int gl = 128; gl <= kGroupMaxLen; gl += 128) {
+    const int gl_max = heads <= kGroupVeryFewHeads ? kGroupMaxLenVeryFew : kGroupMaxLen;
+    for (int gl = 128; gl <= gl_max; gl += 128) {
       const int n = ceil_div(p->max_len, gl);
-      if (n > 1 && n <= mkv::kMaxGroups && heads * n <= kGroupWgs) {
+      if (n > 1 && n <= mkv::kMaxGroups && heads * n <= kGroupWgs &&
+          (gl < mkv::kGroupWideLen || heads * (n + 1) <= kCUs)) {
         *split_len = gl;
         *nsplit = n;
         return mkv::kDecodeGroup;
@@ -63,8 +75,8 @@ mkv::DecodeShape decode_shape(const mkv_decode_params* p, int* split_len, int* n
   *split_len = sl;
   *nsplit = ceil_div(p->max_len, sl);
   if (p->n_split == 1) return mkv::kDecodeFused;
-  if (p->n_split == 0 && (p->max_len <= kFusedMaxLenMany || (heads <= kCUs && p->max_len <= kFusedMaxLenFull)))
-    return mkv::kDecodeFused;
+  const int fused_max = heads > kCUs ? kFusedMaxLenMany : heads > kCUs / 2 ? kFusedMaxLenFull : kFusedMaxLenHalf;
+  if (p->n_split == 0 && p->max_len <= fused_max) return mkv::kDecodeFused;
   return mkv::kDecodeSlices;
 }
 
