@@ -80,7 +80,7 @@ def compress_kernel_work(n_heads: int, G: int, w: int, N: int, d: int, n_sink: i
     context, for one call over `n_heads` KV heads (C = N - w - n_sink candidates):
       k_rows_cov   K and V read once; window logits 2 G w N d (MFMA) and the candidate
                    covariance V_C^T K_C, 2 |C| d^2 (MFMA);
-      k_mass       K read once; the window logits again, 2 G w N d (MFMA);
+      k_mass(_stream) K read once; the window logits again, 2 G w N d (MFMA);
       k_residual   K and V of the candidates read once; S_tilde0 k_j for every candidate on
                    two bf16 planes, 2 x 2 |C| d^2 (MFMA)."""
     C = N - w - n_sink
@@ -89,6 +89,7 @@ def compress_kernel_work(n_heads: int, G: int, w: int, N: int, d: int, n_sink: i
     return {"k_rows_cov": {"bytes": 2 * N * d * elem * n_heads, "flops": logits + cov,
                            "covariance_flops": cov},
             "k_mass": {"bytes": N * d * elem * n_heads, "flops": logits},
+            "k_mass_stream": {"bytes": N * d * elem * n_heads, "flops": logits},
             "k_residual": {"bytes": 2 * C * d * elem * n_heads, "flops": 2 * cov}}
 
 
@@ -899,7 +900,7 @@ def main() -> int:
         "compress_ms_per_layer": {k: v["compress_ms_per_layer"] for k, v in per_budget.items()},
         "per_budget": per_budget,
         "roofline": {"kernel": "momentkv_decode_attn call over the stack: one launch, "
-                               "k_decode_fused (max_len <= 384) or k_decode_slice (the last "
+                               "k_decode_fused, k_decode_group or k_decode_slice (the last "
                                "wave of each head merges it); time per call from the graph "
                                "replays",
                      "bound": "hbm", "achieved": avg_bytes / avg_launch_s / 1e9,
