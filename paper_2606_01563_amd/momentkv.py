@@ -229,13 +229,22 @@ def _pointers(required, optional) -> list | None:
     return ptrs
 
 
-@functools.lru_cache(maxsize=512, typed=True)
-def _decode_plan(*fields):
-    """The parameter block of these values (read only: shared by the calls that have them),
-    and its workspace sizes: decode, its zero prefix, eviction."""
+def _new_plan(*fields):
     p = DecodeParams(*fields)
     return (p, momentkv_decode_workspace_bytes(p), momentkv_decode_workspace_zero_bytes(p),
             momentkv_decode_evict_workspace_bytes(p))
+
+
+_PLAIN = frozenset((int, float))
+_kept_plan = functools.lru_cache(maxsize=512, typed=True)(_new_plan)
+
+
+def _decode_plan(*fields):
+    """The parameter block of these values (read only: shared by the calls that have them),
+    and its workspace sizes: decode, its zero prefix, eviction.  Plain numbers only are kept:
+    anything else that converts to a number (a 0-d tensor or array) may hold another one at
+    the next call, and is read at every call."""
+    return _kept_plan(*fields) if _PLAIN.issuperset(map(type, fields)) else _new_plan(*fields)
 
 
 def _workspace(nbytes: int, device, ws: torch.Tensor | None) -> torch.Tensor:

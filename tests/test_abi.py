@@ -7,7 +7,9 @@ is ever enqueued.
 import ctypes
 import os
 
+import numpy as np
 import pytest
+import torch
 
 from paper_2606_01563_amd import momentkv as mk
 
@@ -341,3 +343,20 @@ def test_decode_plan_of_equal_values_of_other_types_is_refused():
     assert mk._decode_plan(*ok)[1] > 0
     with pytest.raises(TypeError):
         mk._decode_plan(*ok[:5], 128.0, *ok[6:])
+
+
+@pytest.mark.parametrize("make", [torch.tensor, np.array], ids=["tensor", "array"])
+def test_decode_plan_reads_number_like_objects_at_every_call(make):
+    """A 0-d tensor or array as scale, tau or max_len is what it holds at the call, also when
+    it was changed in place since the last one."""
+    scale, tau, max_len = make(0.125), make(1e-6), make(128)
+    fields = lambda: (1, 4, 1, 64, 4096, max_len, 1, 1, scale, tau, 0, 0)
+    p, nbytes = mk._decode_plan(*fields())[:2]
+    assert (p.scale, p.max_len) == (0.125, 128) and abs(p.tau - 1e-6) < 1e-12
+    scale *= 2
+    tau *= 1000
+    max_len += 1872
+    q, more = mk._decode_plan(*fields())[:2]
+    assert (q.scale, q.max_len) == (0.25, 2000) and abs(q.tau - 1e-3) < 1e-9
+    assert more == mk._decode_plan(1, 4, 1, 64, 4096, 2000, 1, 1, 0.25, 1e-3, 0, 0)[1] > nbytes
+    assert (p.scale, p.max_len) == (0.125, 128)  # the earlier call's block is its own
