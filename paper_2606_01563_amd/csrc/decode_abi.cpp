@@ -50,10 +50,19 @@ constexpr int kGroupWgs = 192, kGroupMaxLen = 384;
 constexpr int kGroupVeryFewHeads = 32, kGroupMaxLenVeryFew = 768;
 
 // ----------------------------------------------------------------------- decode
-// Token slices per KV head.  Slices shape with n_split = 0: about kDecodeWaves single-wave
-// slices in the whole grid (three per CU), at least 32 rows each.  Measured on a 288-head
-// stack, longer slices (fewer partials to merge) beat finer splits once every CU holds a
-// few slices.  Rows per slice are a multiple of the 32-row block.
+// Token slices per KV head of the slices shape.  With n_split = 0: about kDecodeWaves
+// single-wave slices in the whole grid (three per CU), at least 32 rows each.  Measured on a
+// 288-head stack, longer slices (fewer partials to merge) beat finer splits once every CU
+// holds a few slices.  Rows per slice are a multiple of the 32-row block.
+void slice_split(const mkv_decode_params* p, int* split_len, int* nsplit) {
+  const int64_t heads = (int64_t)p->batch * p->n_kv_heads;
+  const int want = p->n_split > 0 ? p->n_split
+                                  : (int)std::min<int64_t>(std::max<int64_t>((kDecodeWaves + heads - 1) / heads, 1), 1 << 20);
+  const int sl = ceil_div(p->max_len, want);
+  *split_len = std::max(32, ceil_div(sl, 32) * 32);
+  *nsplit = ceil_div(p->max_len, *split_len);
+}
+
 mkv::DecodeShape decode_shape(const mkv_decode_params* p, int* split_len, int* nsplit) {
   const int64_t heads = (int64_t)p->batch * p->n_kv_heads;
   if (p->n_split == 0 && p->max_len > kFusedMaxLen) {
@@ -68,12 +77,7 @@ mkv::DecodeShape decode_shape(const mkv_decode_params* p, int* split_len, int* n
       }
     }
   }
-  const int want = p->n_split > 0 ? p->n_split
-                                  : (int)std::min<int64_t>(std::max<int64_t>((kDecodeWaves + heads - 1) / heads, 1), 1 << 20);
-  int sl = ceil_div(p->max_len, want);
-  sl = std::max(32, ceil_div(sl, 32) * 32);
-  *split_len = sl;
-  *nsplit = ceil_div(p->max_len, sl);
+  slice_split(p, split_len, nsplit);
   if (p->n_split == 1) return mkv::kDecodeFused;
   const int fused_max = heads > kCUs ? kFusedMaxLenMany : heads > kCUs / 2 ? kFusedMaxLenFull : kFusedMaxLenHalf;
   if (p->n_split == 0 && p->max_len <= fused_max) return mkv::kDecodeFused;
@@ -124,14 +128,20 @@ mkv::DecodeArgs decode_layout(const mkv_decode_params* p, void* ws, size_t* tota
   a.nsq = p->order >= 1 ? p->head_dim / 32 : 0;
   a.summary = p->summary;
   const size_t H = a.n_heads, D = p->head_dim, G = a.G;
+  // Every shape reserves the partials of the slices shape (a group launch has fewer, one
+  // workgroup per head none), so that the bytes grow with max_len as they would without the
+  // choice of a shape: a workspace sized for long caches serves the calls on shorter ones.
+  int slice_len = 0, slices = 0;
+  slice_split(p, &slice_len, &slices);
+  const size_t parts = std::max(slices, a.nsplit);
   Carver c;
   c.base = static_cast<char*>(ws);
   // The leading bytes (the flag, then one arrival counter per head) are zero-filled by
   // the caller before first use; every call leaves the counters at zero.
   a.flag = c.take<int32_t>(sizeof(int32_t));
   a.cnt = c.take<int32_t>(std::max<size_t>(cnt_slots, H) * sizeof(int32_t));
-  a.part_o = c.take<float>(H * a.nsplit * G * D * sizeof(float));
-  a.part_ml = c.take<float>(H * a.nsplit * G * 2 * sizeof(float));
+  a.part_o = c.take<float>(H * parts * G * D * sizeof(float));
+  a.part_ml = c.take<float>(H * parts * G * 2 * sizeof(float));
   a.sq = c.take<float>(H * G * D * sizeof(float));
   *total = c.off;
   return a;

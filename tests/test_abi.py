@@ -360,3 +360,30 @@ def test_decode_plan_reads_number_like_objects_at_every_call(make):
     assert (q.scale, q.max_len) == (0.25, 2000) and abs(q.tau - 1e-3) < 1e-9
     assert more == mk._decode_plan(1, 4, 1, 64, 4096, 2000, 1, 1, 0.25, 1e-3, 0, 0)[1] > nbytes
     assert (p.scale, p.max_len) == (0.125, 128)  # the earlier call's block is its own
+
+
+def decode_bytes_of_slices(p):
+    """Flag, counters, and the partials of about 768 slices in the grid (n_split per head if
+    given), each of a multiple of 32 rows."""
+    up = lambda x: -(-x // 256) * 256
+    H, G, d = p.batch * p.n_kv_heads, p.n_q_heads // p.n_kv_heads, p.head_dim
+    want = p.n_split or max(1, -(-768 // H))
+    rows = max(32, 32 * -(-(-(-p.max_len // want)) // 32))
+    n = -(-p.max_len // rows)
+    return 256 + up(4 * H) + up(4 * H * n * G * d) + up(8 * H * n * G) + up(4 * H * G * d)
+
+
+@pytest.mark.parametrize("heads", [(1, 1), (1, 8), (4, 8), (5, 8), (6, 8), (8, 8), (12, 8), (36, 8)])
+def test_decode_workspace_is_that_of_the_slices_for_every_shape(heads):
+    """The bytes do not depend on the launch shape, so a workspace sized for long caches is
+    accepted by calls of other shapes on shorter ones (each pair below is one)."""
+    for d, G in ((64, 1), (128, 4), (128, 16)):
+        size = {}
+        for rows in (1, 200, 256, 257, 300, 384, 512, 640, 700, 1024, 1152, 2048, 4096, 32768):
+            for n_split in (0, 1, 3):
+                p = dparams(batch=heads[0], n_kv_heads=heads[1], n_q_heads=G * heads[1],
+                            head_dim=d, cap=rows, max_len=rows, n_split=n_split)
+                size[rows, n_split] = mk.momentkv_decode_workspace_bytes(p)
+                assert size[rows, n_split] == decode_bytes_of_slices(p), (heads, d, G, rows)
+        for long, short in ((1024, 256), (2048, 256), (1152, 200), (700, 300), (32768, 512)):
+            assert size[long, 0] >= size[short, 0], (heads, d, G, long, short)
