@@ -207,11 +207,13 @@ size_t momentkv_decode_workspace_bytes(const mkv_decode_params* p);
 size_t momentkv_decode_workspace_size(const mkv_decode_params* p);
 
 /* Leading bytes of that workspace that must be zero before a call (0 on invalid
- * parameters): the sticky flag, then one arrival counter per KV head that the split shape
- * uses to find the last slice of a head to finish.  Every call leaves the counters at zero,
- * so a workspace zeroed once serves any number of calls; a workspace reused for a call
- * with a larger value here needs the bytes beyond the previous value zeroed first (they
- * may hold partial results of earlier calls). */
+ * parameters): 256 bytes with the sticky flag (the first int32) and the arrival counters of
+ * token groups, then one arrival counter per KV head for token slices; they find the last
+ * workgroup of a head to finish.  Every call leaves the counters at zero, so a workspace
+ * zeroed once serves any number of calls with one number of heads.  A call may leave partial
+ * results in the bytes after its own value here: before a call with a larger value on the
+ * same workspace, zero the bytes beyond the previous call's value (a later call that finds
+ * other than zero there leaves heads unmerged: their outputs and lens are not written). */
 size_t momentkv_decode_workspace_zero_bytes(const mkv_decode_params* p);
 
 /* Decode form of a summary (Eq. fhat's covariance term; clamp of App. C.2).

@@ -998,7 +998,11 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_decode_group(Decod
   // count in; the last workgroup of the head merges it
   stores_complete();
   __syncthreads();
-  if (threadIdx.x == 0) s_last = atomicAdd(a.cnt + head, 1) == (n_sq > 0) + a.nsplit - 1;
+  const int arr_shift = 16 * (head & 1);  // two heads per counter word
+  if (threadIdx.x == 0) {
+    const uint32_t prior = atomicAdd(a.group_cnt + (head >> 1), 1u << arr_shift);
+    s_last = (int)((prior >> arr_shift) & 0xFFFFu) == (n_sq > 0) + a.nsplit - 1;
+  }
   __syncthreads();
   if (!s_last) return;
   loads_after_count();
@@ -1061,7 +1065,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_decode_group(Decod
   }
   if (threadIdx.x == 0) {
     // every other workgroup of the head has counted itself in, and so has read lens
-    __hip_atomic_store(a.cnt + head, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    atomicAnd(a.group_cnt + (head >> 1), 0xFFFF0000u >> arr_shift);
   }
   __syncthreads();  // every wave has read lens
   if (threadIdx.x == 0 && hl.can_append) a.lens[head] = hl.old_len + 1;

@@ -48,6 +48,7 @@ constexpr int kFusedMaxLenHalf = 640;   // up to kCUs / 2 heads
 constexpr int kFusedMaxLenFull = 1024;  // kCUs / 2 to kCUs heads
 constexpr int kGroupWgs = 192, kGroupMaxLen = 384;
 constexpr int kGroupVeryFewHeads = 32, kGroupMaxLenVeryFew = 768;
+static_assert(kGroupWgs / 2 <= mkv::kMaxGroupHeads, "at least two groups per head");
 
 // ----------------------------------------------------------------------- decode
 // Token slices per KV head of the slices shape.  With n_split = 0: about kDecodeWaves
@@ -136,13 +137,28 @@ mkv::DecodeArgs decode_layout(const mkv_decode_params* p, void* ws, size_t* tota
   const size_t parts = std::max(slices, a.nsplit);
   Carver c;
   c.base = static_cast<char*>(ws);
-  // The leading bytes (the flag, then one arrival counter per head) are zero-filled by
-  // the caller before first use; every call leaves the counters at zero.
+  // The leading bytes (the flag and the group launch's counters in its block, then one
+  // arrival counter per head) are zero-filled by the caller before first use; every call
+  // leaves the counters at zero.
   a.flag = c.take<int32_t>(sizeof(int32_t));
+  a.group_cnt = a.flag ? reinterpret_cast<uint32_t*>(a.flag) + 1 : nullptr;
   a.cnt = c.take<int32_t>(std::max<size_t>(cnt_slots, H) * sizeof(int32_t));
-  a.part_o = c.take<float>(H * parts * G * D * sizeof(float));
-  a.part_ml = c.take<float>(H * parts * G * 2 * sizeof(float));
-  a.sq = c.take<float>(H * G * D * sizeof(float));
+  auto take_parts = [&](size_t n) {
+    a.part_o = c.take<float>(H * n * G * D * sizeof(float));
+    a.part_ml = c.take<float>(H * n * G * 2 * sizeof(float));
+    a.sq = c.take<float>(H * G * D * sizeof(float));
+  };
+  const size_t first = c.off;
+  take_parts(parts);
+  if (a.shape == kDecodeGroup) {
+    // The group launch's few partials at the end of the reservation: away from the leading
+    // bytes, where a call with more heads on the same workspace has its counters.
+    const size_t end = c.off;
+    c.off = first;
+    take_parts(a.nsplit);
+    c.off = first + (end - c.off);
+    take_parts(a.nsplit);
+  }
   *total = c.off;
   return a;
 }

@@ -359,6 +359,7 @@ def momentkv_compress(q_win: torch.Tensor, k: torch.Tensor, v: torch.Tensor, bud
         code = lib().momentkv_compress(ctypes.byref(p), *([None] * 11), None, None, 0, None)
         raise MomentKVError(code, "momentkv_compress")
     ws = _workspace(nbytes, dev, workspace)
+    _wrote_workspace(ws, 0)
     code = lib().momentkv_compress(
         ctypes.byref(p), _ptr(q_win), _ptr(k), _ptr(v), _ptr(out.k_out), _ptr(out.v_out),
         _ptr(out.idx), _ptr(out.lens), _ptr(out.n_e), _ptr(out.s_k), _ptr(out.s_v), _ptr(out.S),
@@ -375,11 +376,20 @@ def momentkv_decode_workspace_zero_bytes(p: DecodeParams) -> int:
 
 
 def _zero_prefix(ws: torch.Tensor, nbytes: int) -> None:
-    """Zeroes the leading nbytes of a decode workspace unless this tensor object is known
-    to have them at zero already (zeroed here before; calls leave them at zero)."""
-    if getattr(ws, "_mkv_zeroed", 0) < nbytes:
-        ws[:nbytes].zero_()
+    """Zeroes what is not known to be zero of the leading nbytes of a decode workspace.  After
+    the call these are at zero again, and what follows them may hold its partial results,
+    which a later call with more heads has under its counters."""
+    known = getattr(ws, "_mkv_zeroed", 0)
+    if known < nbytes:
+        ws[known:nbytes].zero_()
+    if known != nbytes:
         ws._mkv_zeroed = nbytes
+
+
+def _wrote_workspace(ws: torch.Tensor | None, start: int) -> None:
+    """A call other than the decode wrote into `ws` from byte `start` on."""
+    if ws is not None and getattr(ws, "_mkv_zeroed", 0) > start:
+        ws._mkv_zeroed = start
 
 
 def decode_params(q, k_cache, *, max_len, order=1, scale=0.0, tau=1e-6,
@@ -521,8 +531,8 @@ def momentkv_decode_attn(q: torch.Tensor, k_cache: torch.Tensor, v_cache: torch.
     `max_len` bounds lens after the append (defaults to the cache capacity).  The first
     int32 of the workspace is the sticky append-overflow flag.  The leading
     momentkv_decode_workspace_zero_bytes(p) bytes (the flag and the per-head arrival
-    counters) are zeroed here the first time a workspace tensor is used with this prefix
-    length (the flag included); calls leave the counters at zero.
+    counters) are zeroed here the first time a workspace tensor is used, and the counters
+    past those of the tensor's last call whenever it had fewer heads.
     """
     ptr = _decode_pointers(q, k_cache, v_cache, lens, n_e, s_k, s_v, S, k_new, v_new, out, lse,
                            w_r, workspace, summary)
@@ -602,6 +612,7 @@ def momentkv_decode_evict(q: torch.Tensor, k_cache: torch.Tensor, v_cache: torch
     ws = _workspace(nbytes, q.device, workspace)
     if fresh:
         ws[:256].zero_()  # the sticky flag
+    _wrote_workspace(ws, 256)
     code = lib().momentkv_decode_evict(ctypes.byref(p), int(budget), *ptr[:4], ptr[8], ptr[9],
                                        *ptr[4:8], *ptr[10:14], ws.data_ptr(), ws.numel(), _stream())
     if code != 0:

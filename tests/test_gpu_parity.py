@@ -244,6 +244,71 @@ def test_decode_token_groups_repeat_bit_exact(G):
     assert torch.equal(na, ref)
 
 
+def _decode_state(Hkv, G, d, rows, seed, batch=1):
+    """Random caches of `rows` rows with summaries: (q, k, v, lens, n_e, s_k, s_v, S)."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    r = lambda *s: torch.randn(*s, device="cuda", generator=g)
+    i = lambda lo, hi: torch.randint(lo, hi, (batch, Hkv), device="cuda", generator=g, dtype=torch.int32)
+    kc, vc = r(batch, Hkv, rows, d).to(torch.bfloat16), r(batch, Hkv, rows, d).to(torch.bfloat16)
+    return (r(batch, Hkv * G, d).to(torch.bfloat16), kc, vc, i(rows // 2, rows), i(0, 900),
+            r(batch, Hkv, d) * 30, r(batch, Hkv, d) * 30, r(batch, Hkv, d, d) * 50)
+
+
+@pytest.mark.parametrize("few", ["groups", "slices", "evict"])
+@pytest.mark.parametrize("replayed", [False, True])
+def test_decode_after_a_call_with_fewer_heads_on_the_same_workspace(few, replayed):
+    """Slices of 288 heads, then on the same workspace a call with 8 heads (token groups at 300
+    rows, slices, an eviction), whose partials or records lie where the 288 heads have their
+    counters, then the 288 heads again: the bits of a call on a workspace of its own, the
+    sticky flag untouched.  Replayed: both calls captured, so nothing is zeroed between them
+    (which slices and evictions of fewer heads need)."""
+    if replayed and few != "groups":
+        pytest.skip("needs the counters zeroed between the calls")
+    many = _decode_state(8, 1, 64, 700, 1, batch=36)
+    small = _decode_state(8, 4, 128, 300, 2)
+    ref = mk.momentkv_decode_attn(*many)[0].clone()
+    ref_small = mk.momentkv_decode_attn(*small)[0].clone()
+    p = mk.decode_params(many[0], many[1], max_len=700)
+    ws = torch.zeros(mk.momentkv_decode_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    out, out_small = torch.empty_like(many[0]), torch.empty_like(small[0])
+    many_call = lambda: mk.momentkv_decode_attn(*many, out=out, workspace=ws)
+    assert many_call()[3] is ws
+    if few == "evict":
+        new = torch.zeros(1, 8, 128, dtype=torch.bfloat16, device="cuda")
+        few_call = lambda: mk.momentkv_decode_evict(*small, new, new, 100, workspace=ws)[4]
+    else:
+        few_call = lambda: mk.momentkv_decode_attn(*small, n_split=4 if few == "slices" else 0,
+                                                   out=out_small, workspace=ws)[3]
+    if replayed:
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            few_call()
+        torch.cuda.current_stream().wait_stream(side)
+        many_call()
+        torch.cuda.synchronize()
+        graphs = [torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()]
+        for graph, call in zip(graphs, (many_call, few_call)):
+            with torch.cuda.graph(graph):
+                call()
+        many_call, few_call = graphs[0].replay, graphs[1].replay
+    if few != "evict":  # an append to a full cache sets the flag (bit 0)
+        ws[:4].view(torch.int32).fill_(1)
+    for rep in range(3):
+        announce(f"{few} replayed={replayed} repetition {rep}")
+        got = few_call()
+        assert replayed or got is ws
+        out.zero_()
+        many_call()
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref), rep
+        assert int(ws[4:256].sum()) == 0
+        if few != "evict":
+            assert int(ws[:4].view(torch.int32)[0]) == 1
+        if few == "groups":
+            assert torch.equal(out_small, ref_small), rep
+
+
 # ---------------------------------------------------------------- edge cases
 @pytest.mark.parametrize("summary", [0, 1])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])

@@ -11,6 +11,7 @@ import sys
 import pytest
 import torch
 
+from paper_2606_01563_amd import momentkv as mk
 from paper_2606_01563_amd import synth
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -115,3 +116,24 @@ def test_needle_queries_concentrate_attention():
     needles = set(int(p) for p in x["needles"][0, 0])
     assert all(int(i) in needles for i in s.argmax(dim=1))
     assert float((top / bg_std).min()) > 5.0
+
+
+def test_counters_past_the_last_calls_are_zeroed_for_a_call_with_more_heads():
+    """A decode call zeroes of its prefix what calls since (with fewer heads, or of another
+    kind) may have written over, and leaves the sticky flag in the first bytes alone."""
+    ws = torch.full((4096,), 7, dtype=torch.uint8)
+    mk._zero_prefix(ws, 1536)
+    assert int(ws[:1536].sum()) == 0 and int(ws[1536:].min()) == 7
+    ws[0] = 1                                     # the flag, set by a call
+    mk._zero_prefix(ws, 512)
+    ws[512:] = 9                                  # that call's partial results
+    mk._zero_prefix(ws, 1536)
+    assert int(ws[0]) == 1 and int(ws[1:1536].sum()) == 0 and int(ws[1536:].min()) == 9
+    ws[256:] = 5                                  # an eviction's records
+    mk._wrote_workspace(ws, 256)
+    mk._zero_prefix(ws, 1024)
+    assert int(ws[0]) == 1 and int(ws[1:1024].sum()) == 0 and int(ws[1024:].min()) == 5
+    ws[:] = 3                                     # a compression
+    mk._wrote_workspace(ws, 0)
+    mk._zero_prefix(ws, 1024)
+    assert int(ws[:1024].sum()) == 0
