@@ -63,15 +63,29 @@ __device__ __forceinline__ uint32_t score_key(float s) {
   return (u & 0x80000000u) ? 0u : u;  // -0 and negatives sort as 0
 }
 
-// Bins of the per-head histogram: 64 per octave from 2^-28 to 2^4, where the k-th score of
-// a mass that sums to at most one falls for values of any usual scale (keys outside land in
-// the end bins: the selection stays exact, over more candidates).  Eight bins per octave
-// over all exponents left eight times the candidates at the threshold.
+// Bins of the per-head histogram: 64 per octave from 2^-26 to 2^2, where the k-th score of
+// an attention spread over many tokens falls for values of any usual scale, and one per
+// octave below and above (sharp attention, whose scores run over a hundred octaves, and
+// values of other scales).  Eight bins per octave over all exponents left eight times the
+// candidates at the threshold.
 constexpr int TK_HBINS = 2048;
-constexpr int TK_SHIFT = 17;
-constexpr int TK_BASE = (127 - 28) << (23 - TK_SHIFT);
+constexpr int TK_FINE = 17, TK_COARSE = 23;                        // log2 of the keys per bin
+constexpr int TK_FINE_LO = (127 - 26) << (23 - TK_FINE);           // key >> TK_FINE of 2^-26,
+constexpr int TK_FINE_HI = (127 + 2) << (23 - TK_FINE);            // and of 2^2
+constexpr int TK_LOW = TK_FINE_LO >> (TK_COARSE - TK_FINE);        // coarse bins below
+constexpr int TK_HIGH = TK_LOW + TK_FINE_HI - TK_FINE_LO;          // first coarse bin above
+constexpr int TK_HIGH_OFF = TK_HIGH - (TK_FINE_HI >> (TK_COARSE - TK_FINE));
+static_assert(TK_HIGH_OFF + 255 < TK_HBINS, "keys have 31 bits");
 __device__ __forceinline__ int key_bin(uint32_t key) {
-  return min(max((int)(key >> TK_SHIFT) - TK_BASE, 0), TK_HBINS - 1);
+  const int fine = (int)(key >> TK_FINE), coarse = (int)(key >> TK_COARSE);
+  return fine < TK_FINE_LO ? coarse : (fine < TK_FINE_HI ? fine - TK_FINE_LO + TK_LOW : coarse + TK_HIGH_OFF);
+}
+// A bin's lowest key, and log2 of its keys.
+__device__ __forceinline__ bool bin_fine(int b) { return b >= TK_LOW && b < TK_HIGH; }
+__device__ __forceinline__ int bin_shift(int b) { return bin_fine(b) ? TK_FINE : TK_COARSE; }
+__device__ __forceinline__ uint32_t bin_low(int b) {
+  return bin_fine(b) ? (uint32_t)(b - TK_LOW + TK_FINE_LO) << TK_FINE
+                     : (uint32_t)(b < TK_LOW ? b : b - TK_HIGH_OFF) << TK_COARSE;
 }
 
 // Candidates kept by a head: the uniform k_keep, or its head-adaptive share (clamped to
@@ -1028,8 +1042,8 @@ __global__ void __launch_bounds__(256, 2) k_mass_stream(CompressArgs a) {
 //   k_tk_cand   slices x heads: from the head's histogram, the bin B of the k-th largest
 //               key and the count of keys above B (every slice finds the same); hands over
 //               the slice's count of keys above B and its (key, position) pairs inside B
-//               (the candidates: B spans 1/64 of an octave).  The head's last workgroup to
-//               arrive selects among the candidates:
+//               (the candidates: B spans 1/64 of an octave where scores usually are).  The
+//               head's last workgroup to arrive selects among the candidates:
 //               the k-th key T, the last position P kept of the keys equal to T (the lowest
 //               are), and every slice's output offset;
 //   k_tk_write  slices x heads: the slice's kept positions in order (key > T, or = T up to
@@ -1038,6 +1052,12 @@ __global__ void __launch_bounds__(256, 2) k_mass_stream(CompressArgs a) {
 // last workgroup's reads).  With bins of an eighth of an octave, and the refinement repeated
 // by every slice's workgroup (its LDS left one per CU), the two launches took 21.2 / 23.8 /
 // 53 us for 8 heads of 8K / 32K / 128K; now 18.7 / 19.9 / 29.4.
+// A bin of more than TK_CAND_LDS candidates (values far from any usual scale, equal scores,
+// a layer's worth of candidates for the head-adaptive budgets) is handed over grouped by 512
+// sub-bins, so that the last workgroup reads only the sub-bin of the k-th key.  Whole calls
+// with needle queries four times as large, 8 heads of 32K / 128K, with eight bins per octave,
+// then with two end bins refined from memory, then now: 147 / 473 / 142 and 495 / 2399 / 440
+// us; head-adaptive 200 / 2166 / 173 and 586 / 11811 / 495.
 // ------------------------------------------------------------------------------------
 // Exclusive scan of one int per thread over an NT-thread block; the total goes to *total.
 // sW holds NT / 64 ints.
@@ -1118,83 +1138,200 @@ __device__ __forceinline__ void slice_keys(const float* s, int n, int sl, uint32
   }
 }
 
-// The head's selection by the last workgroup to arrive (see above): the candidates and the
-// per-wave counts are read with agent-scope loads.  Up to TK_CAND_LDS candidates are held
-// in LDS (more only where k or the ties at the threshold run to tens of thousands, or the
-// threshold lies in an end bin: the passes then read them from memory, eight loads in
-// flight per thread).
+// A slice's hand-over: up to TKS candidates, then (large bins) the offsets of the 512
+// sub-bins among them as 16-bit halves.
+constexpr int TK_SUB = 512;
+constexpr int TK_STRIDE = kTkSliceWords;  // in 8-byte words
+static_assert(TK_STRIDE == TKS + TK_SUB / 4, "candidates and sub-bin offsets of a slice");
+
 struct TkLds {
   union {
     __align__(16) uint32_t hist[TK_HBINS];  // the head's histogram,
     uint64_t cand[TK_CAND_LDS];             // then its candidates
   };
-  __align__(16) uint32_t digit[2][512];
-  int in_bin[TK_MAX_SLICES];  // candidates kept per slice
+  __align__(16) uint32_t digit[2][TK_SUB];
+  uint32_t kept[2 * TK_MAX_SLICES];  // per slice: candidates above the k-th key, equal to it
   int start[TK_MAX_SLICES + 1];  // the slices' candidates, flattened
+  uint16_t first[TK_MAX_SLICES]; // a slice's first candidate of the sub-bin
+  uint64_t bits[TKS / 64];       // a slice's positions with the k-th key
   uint16_t n_c[64];
-  int W[TKT / 64], last, over;
+  int W[TKT / 64], last, over, sub, cut, rank, P;
 };
 
-__device__ __forceinline__ void tk_finish(TkLds& L, int head, int k, int ntk, int B, int above,
+// One more in counter d[i] for every active lane; a wave of equal counters (equal keys) takes
+// one addition.
+__device__ __forceinline__ void lds_count(uint32_t* d, int i) {
+  const uint64_t on = __ballot(true);
+  const int i0 = __builtin_amdgcn_readfirstlane(i);
+  if (__ballot(i == i0) != on) atomicAdd(&d[i], 1u);
+  else if ((on & ((1ull << (threadIdx.x & 63)) - 1ull)) == 0ull) atomicAdd(&d[i0], (uint32_t)__popcll(on));
+}
+
+// The slice's counts (keys above bin B, and in it) and its candidates of a large bin, grouped
+// by the bin's 512 sub-bins (ascending), with the sub-bins' offsets among them.
+__device__ __forceinline__ void tk_post_grouped(TkLds& L, const uint32_t (&key)[TKPT], int n, int B, int j0,
+                                                uint64_t* cnt, uint64_t* c) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const uint32_t low = bin_low(B);
+  const int ss = bin_shift(B) - 9;
+  for (int i = tid; i < TK_SUB; i += TKT) L.digit[0][i] = 0;
+  if (tid == 0) L.over = 0;
+  __syncthreads();
+  int sub[TKPT], n_gt = 0, n_in = 0, lo = TK_SUB, neg_hi = 1;  // sub-bins (-1: another bin)
+#pragma unroll
+  for (int u = 0; u < TKPT; ++u) {
+    const int b = j0 + u < n ? key_bin(key[u]) : -1;
+    n_gt += b > B;
+    n_in += b == B;
+    sub[u] = b == B ? (int)((key[u] - low) >> ss) : -1;
+    lo = b == B ? min(lo, sub[u]) : lo;
+    neg_hi = min(neg_hi, -sub[u]);
+  }
+  if (n_gt) atomicAdd(&L.over, n_gt);
+  // equal keys throughout the wave: one addition for it
+  const int one = wave_min_i(lo);
+  const bool same = one == -wave_min_i(neg_hi);
+  const int before = wave_incl_scan(n_in) - n_in;  // of the wave's candidates
+  if (same) {
+    if (lane == 63) atomicAdd(&L.digit[0][one], (uint32_t)(before + n_in));
+  } else {
+#pragma unroll
+    for (int u = 0; u < TKPT; ++u)
+      if (sub[u] >= 0) atomicAdd(&L.digit[0][sub[u]], 1u);
+  }
+  __syncthreads();
+  static_assert(TK_SUB == 2 * TKT, "two sub-bins per thread");
+  const int c0 = (int)L.digit[0][2 * tid], c1 = (int)L.digit[0][2 * tid + 1];
+  int n_c;
+  const int e = block_excl_scan<TKT>(c0 + c1, L.W, &n_c);
+  if (tid == 0) st_agent_u64(cnt, (uint64_t)(uint32_t)L.over | ((uint64_t)n_c << 32));
+  L.digit[1][2 * tid] = (uint32_t)e;
+  L.digit[1][2 * tid + 1] = (uint32_t)(e + c0);
+  st_agent_u32(reinterpret_cast<uint32_t*>(c + TKS) + tid, (uint32_t)e | ((uint32_t)(e + c0) << 16));
+  __syncthreads();
+  uint32_t p[TKPT];
+  if (same) {
+    uint32_t base = 0u;
+    if (lane == 63) base = atomicAdd(&L.digit[1][one], (uint32_t)(before + n_in));
+    p[0] = (uint32_t)__builtin_amdgcn_readlane((int)base, 63) + (uint32_t)before;
+#pragma unroll
+    for (int u = 1; u < TKPT; ++u) p[u] = p[u - 1] + (sub[u - 1] >= 0);
+  } else {
+#pragma unroll
+    for (int u = 0; u < TKPT; ++u)
+      if (sub[u] >= 0) p[u] = atomicAdd(&L.digit[1][sub[u]], 1u);
+  }
+#pragma unroll
+  for (int u = 0; u < TKPT; ++u)
+    if (sub[u] >= 0) st_agent_u64(c + p[u], ((uint64_t)key[u] << 32) | (uint32_t)(j0 + u));
+}
+
+// The head's selection by the last workgroup to arrive (see above): the candidates and the
+// per-slice counts are read with agent-scope loads.  Bins of up to TK_CAND_LDS candidates
+// are held in LDS whole.  Of a larger bin (an octave's, very many keys, or equal ones) only the sub-bin of the k-th key is: the sums of the slices' offsets give the sub-bin and
+// its range in every slice.  Where that still has more candidates (equal keys, nearly: one
+// sub-bin spans 2^-15 of its keys' value, or 2^-9 in an octave's bin), a pass reads them
+// from memory, a wave taking a slice at a time with 16 loads in flight per lane.
+template <bool GROUPED>
+__device__ __forceinline__ void tk_finish(TkLds& L, int head, int k, int ntk, int B, int above, int n_bin,
                                           const uint64_t* cnt, const uint64_t* cand, int* sel,
                                           int* off) {
   constexpr int U = 8;
   constexpr int SPT = TK_MAX_SLICES / TKT;  // slices per thread, consecutive
   constexpr int FC = 32;                    // first candidates of a slice
-  const int tid = threadIdx.x;
-  const uint64_t* ch = cand + (size_t)head * ntk * TKS;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint64_t* ch = cand + (size_t)head * ntk * TK_STRIDE;
   // requests: the slices' counts and, where FC of each slice fit in LDS, the first FC
   // candidates of every slice (a slice seldom has more)
   uint64_t cn[SPT], first[U];
 #pragma unroll
   for (int u = 0; u < SPT; ++u) cn[u] = ld_agent_u64(cnt + (size_t)head * ntk + min(SPT * tid + u, ntk - 1));
-  const bool few = ntk <= TK_CAND_LDS / FC;
+  const bool few = !GROUPED && ntk <= TK_CAND_LDS / FC;
   static_assert(TK_CAND_LDS == TKT * U && TK_CAND_LDS / FC <= 64, "one round of requests");
   if (few) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int e = min(tid + TKT * u, ntk * FC - 1);
-      first[u] = ld_agent_u64(ch + (size_t)(e / FC) * TKS + e % FC);
+      first[u] = ld_agent_u64(ch + (size_t)(e / FC) * TK_STRIDE + e % FC);
     }
   }
-  if (tid == 0) L.over = 0;
-  for (int i = tid; i < 2 * 512; i += TKT) L.digit[0][i] = 0;
-  for (int i = tid; i < ntk; i += TKT) L.in_bin[i] = 0;
+  if (tid == 0) {
+    L.over = 0;
+    L.sub = 0;
+    L.P = INT_MAX;
+  }
+  auto clear_digits = [&]() {
+    for (int i = tid; i < 2 * TK_SUB; i += TKT) L.digit[0][i] = 0;
+  };
+  if constexpr (!GROUPED) clear_digits();
+  for (int i = tid; i < ntk; i += TKT) {
+    L.kept[i] = 0u;
+    L.kept[TK_MAX_SLICES + i] = 0u;
+  }
+  if (tid < TKS / 64) L.bits[tid] = 0ull;
+  // the candidates' keys are low + (fewer than 2^bits); need-th largest of them, of the bin,
+  // or of its sub-bin
+  uint32_t low = bin_low(B);
+  int bits = bin_shift(B), need = k - above;
+  int n2[SPT];  // a slice's candidates
+#pragma unroll
+  for (int u = 0; u < SPT; ++u) n2[u] = SPT * tid + u < ntk ? (int)(cn[u] >> 32) : 0;
+  if constexpr (GROUPED) {
+    uint32_t e0 = 0u, e1 = 0u;  // sub-bins 2 tid and 2 tid + 1: candidates below, over the slices
+    for (int s0 = 0; s0 < ntk; s0 += 16) {
+      uint32_t t[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+        t[u] = ld_agent_u32(reinterpret_cast<const uint32_t*>(ch + (size_t)min(s0 + u, ntk - 1) * TK_STRIDE + TKS) + tid);
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        e0 += s0 + u < ntk ? t[u] & 0xFFFFu : 0u;
+        e1 += s0 + u < ntk ? t[u] >> 16 : 0u;
+      }
+    }
+    L.digit[0][2 * tid] = e0;
+    L.digit[0][2 * tid + 1] = e1;
+    __syncthreads();
+    // the highest sub-bin with at most n_bin - need candidates below it
+    if ((int)e0 <= n_bin - need) atomicMax(&L.sub, (int)e1 <= n_bin - need ? 2 * tid + 1 : 2 * tid);
+    __syncthreads();
+    const int sub = L.sub;
+    need -= n_bin - (sub + 1 < TK_SUB ? (int)L.digit[0][sub + 1] : n_bin);
+    bits -= 9;
+    low += (uint32_t)sub << bits;
+#pragma unroll
+    for (int u = 0; u < SPT; ++u) {
+      const int i = SPT * tid + u;
+      const uint32_t* t = reinterpret_cast<const uint32_t*>(ch + (size_t)min(i, ntk - 1) * TK_STRIDE + TKS);
+      const uint32_t w0 = ld_agent_u32(t + (sub >> 1)), w1 = ld_agent_u32(t + min((sub + 1) >> 1, TK_SUB / 2 - 1));
+      const int o0 = (int)((w0 >> (16 * (sub & 1))) & 0xFFFFu);
+      const int o1 = sub + 1 < TK_SUB ? (int)((w1 >> (16 * ((sub + 1) & 1))) & 0xFFFFu) : n2[u];
+      if (i < ntk) {
+        L.kept[i] = (uint32_t)(n2[u] - o1);  // those of the sub-bins above are kept
+        L.first[i] = (uint16_t)o0;
+        n2[u] = o1 - o0;
+      }
+    }
+  }
   int sum = 0, m, over = 0;
 #pragma unroll
   for (int u = 0; u < SPT; ++u) {
-    const int c = SPT * tid + u < ntk ? (int)(cn[u] >> 32) : 0;
-    over |= c > FC;
-    sum += c;
+    over |= n2[u] > FC;
+    sum += n2[u];
   }
   int acc = block_excl_scan<TKT>(sum, L.W, &m);
 #pragma unroll
   for (int u = 0; u < SPT; ++u) {
-    const int i = SPT * tid + u, c = i < ntk ? (int)(cn[u] >> 32) : 0;
+    const int i = SPT * tid + u;
     if (i < ntk) L.start[i] = acc;
-    if (i < 64) L.n_c[i] = (uint16_t)c;
-    acc += c;
+    if (i < 64) L.n_c[i] = (uint16_t)n2[u];
+    acc += n2[u];
   }
+  if (tid == 0) L.start[ntk] = m;
   if (over) L.over = 1;
+  if constexpr (GROUPED) clear_digits();  // (they held the sub-bins' sums)
   __syncthreads();
-  // candidate f of the head: its slice by bisection over the slices' starts, then the entry
-  int top = 1;
-  while (2 * top < ntk) top *= 2;  // uniform
-  auto fetch = [&](int f0, uint64_t (&c)[U]) {
-    int s2[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) s2[u] = 0;
-    for (int st = top; st >= 1; st >>= 1)
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int t = min(s2[u] + st, ntk - 1);
-        if (L.start[t] <= min(f0 + TKT * u, m - 1)) s2[u] = t;
-      }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      c[u] = ld_agent_u64(ch + (size_t)s2[u] * TKS + (min(f0 + TKT * u, m - 1) - L.start[s2[u]]));
-  };
-  const bool in_lds = m <= TK_CAND_LDS;
+  const bool in_lds = !GROUPED || m <= TK_CAND_LDS;
   if (few && !L.over) {  // uniform; m <= ntk * FC
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -1202,86 +1339,141 @@ __device__ __forceinline__ void tk_finish(TkLds& L, int head, int k, int ntk, in
       if (s2 < ntk && e % FC < (int)L.n_c[s2]) L.cand[L.start[s2] + e % FC] = first[u];
     }
   } else if (in_lds && m > 0) {
+    // candidate f of the head: its slice by bisection over the slices' starts, then the entry
+    int top = 1;
+    while (2 * top < ntk) top *= 2;  // uniform
+    int s2[U];
     uint64_t c[U];
-    fetch(tid, c);
+#pragma unroll
+    for (int u = 0; u < U; ++u) s2[u] = 0;
+    for (int st = top; st >= 1; st >>= 1)
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int t = min(s2[u] + st, ntk - 1);
+        if (L.start[t] <= min(tid + TKT * u, m - 1)) s2[u] = t;
+      }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      c[u] = ld_agent_u64(ch + (size_t)s2[u] * TK_STRIDE + (GROUPED ? L.first[s2[u]] : 0) + (min(tid + TKT * u, m - 1) - L.start[s2[u]]));
 #pragma unroll
     for (int u = 0; u < U; ++u)
       if (tid + TKT * u < m) L.cand[tid + TKT * u] = c[u];
   }
   __syncthreads();
+  // a wave's lanes over the candidates of one slice, in memory
+  auto slice_cands = [&](int s2, auto&& fn) {
+    constexpr int V = 16;
+    const int n = L.start[s2 + 1] - L.start[s2];
+    const uint64_t* c = ch + (size_t)s2 * TK_STRIDE + L.first[s2];
+    for (int f0 = 0; f0 < n; f0 += 64 * V) {
+      uint64_t x[V];
+#pragma unroll
+      for (int v = 0; v < V; ++v) x[v] = ld_agent_u64(c + min(f0 + lane + 64 * v, n - 1));
+#pragma unroll
+      for (int v = 0; v < V; ++v)
+        if (f0 + lane + 64 * v < n) fn(x[v]);
+    }
+  };
   auto for_each_cand = [&](auto&& fn) {
     if (in_lds) {
       for (int f = tid; f < m; f += TKT) fn(L.cand[f]);
-    } else {
-      for (int f0 = 0; f0 < m; f0 += TKT * U) {
-        uint64_t c[U];
-        fetch(f0 + tid, c);
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-          if (f0 + tid + TKT * u < m) fn(c[u]);
-      }
+    } else if constexpr (GROUPED) {
+      for (int s2 = wave; s2 < ntk; s2 += TKT / 64) slice_cands(s2, fn);
     }
   };
-  // The `need`-th largest (on return: the rank among its equals, and their count) of a field
-  // of the candidates that pass a filter, by digits of up to 9 bits below bit `top` (above
-  // it the field is zero).  Two digit histograms, zero on entry, in turn: one is cleared
-  // while the other is filled.
-  int flip = 0;
-  auto select = [&](auto&& field, int top, int& need, int& equal) -> uint32_t {
-    uint32_t prefix = 0u, mask = 0u;
-    for (int hi = top; hi > 0;) {
-      const int shift = max(hi - 9, 0);
-      const uint32_t dm = (1u << (hi - shift)) - 1u;
-      uint32_t* d = L.digit[flip];
-      for_each_cand([&](uint64_t c) {
-        uint32_t x;
-        if (field(c, x) && (x & mask) == prefix) atomicAdd(&d[(x >> shift) & dm], 1u);
-      });
+  // The k-th key, by digits of up to 9 bits: two digit histograms, zero on entry, in turn
+  // (one is cleared while the other is filled).  need becomes its rank among its equals.
+  int flip = 0, equal = 0;
+  uint32_t T = 0u, mask = 0u;
+  for (int hi = bits; hi > 0;) {
+    const int shift = max(hi - 9, 0);
+    const uint32_t dm = (1u << (hi - shift)) - 1u;
+    uint32_t* d = L.digit[flip];
+    for_each_cand([&](uint64_t c) {
+      const uint32_t x = (uint32_t)(c >> 32) - low;
+      if ((x & mask) == T) {
+        if constexpr (GROUPED) lds_count(d, (int)((x >> shift) & dm));
+        else atomicAdd(&d[(x >> shift) & dm], 1u);
+      }
+    });
+    __syncthreads();
+    uint32_t b, ab;  // every wave finds the same digit
+    wave_find_bin<TK_SUB>(d, need, &b, &ab);
+    equal = (int)d[b];
+    T |= b << shift;
+    mask |= dm << shift;
+    need -= (int)ab;
+    flip ^= 1;
+    hi = shift;
+    if (hi > 0) {  // the other buffer was read before the last barrier
       __syncthreads();
-      uint32_t b, ab;  // every wave finds the same digit
-      wave_find_bin<512>(d, need, &b, &ab);
-      equal = (int)d[b];
-      prefix |= b << shift;
-      mask |= dm << shift;
-      need -= (int)ab;
-      flip ^= 1;
-      hi = shift;
-      if (hi > 0) {  // the other buffer was read before the last barrier
-        __syncthreads();
-        for (int i = tid; i < 512; i += TKT) L.digit[flip ^ 1][i] = 0;
-      }
+      for (int i = tid; i < TK_SUB; i += TKT) L.digit[flip ^ 1][i] = 0;
     }
-    return prefix;
-  };
-  // the k-th key: the low bits of a bin inside the range, the whole key in an end bin
-  const bool end_bin = B == 0 || B == TK_HBINS - 1;
-  const uint32_t low = end_bin ? 0u : (uint32_t)(B + TK_BASE) << TK_SHIFT;
-  int need = k - above, equal = 0;
-  const uint32_t T = low + select([&](uint64_t c, uint32_t& x) { x = (uint32_t)(c >> 32) - low; return true; },
-                                  end_bin ? 31 : TK_SHIFT, need, equal);
-  // the last position kept of the keys equal to T: the need-th lowest
-  int P = INT_MAX;
-  if (equal > need) {  // uniform
-    __syncthreads();
-    for (int i = tid; i < 2 * 512; i += TKT) L.digit[0][i] = 0;
-    __syncthreads();
-    constexpr uint32_t PM = (1u << 20) - 1u;  // at most 2^20 positions
-    int nd = need, eq = 0;
-    P = (int)(PM - select([&](uint64_t c, uint32_t& x) { x = PM - (uint32_t)c; return (uint32_t)(c >> 32) == T; }, 20, nd, eq));
   }
+  T += low;
+  // kept per slice: the keys above T, and the need lowest positions of those equal to it
+  const bool cut = equal > need;  // uniform
   for_each_cand([&](uint64_t c) {
     const uint32_t key = (uint32_t)(c >> 32);
-    const int pos = (int)(uint32_t)c;
-    if (key > T || (key == T && pos <= P)) atomicAdd(&L.in_bin[pos / TKS], 1);
+    const int s2 = (int)(uint32_t)c / TKS;
+    if (key >= T) {
+      const int i = s2 + (key > T || !cut ? 0 : TK_MAX_SLICES);
+      if constexpr (GROUPED) lds_count(L.kept, i);
+      else atomicAdd(&L.kept[i], 1u);
+    }
   });
   __syncthreads();
+  if (cut) {
+    // the slice in which the need-th falls, and its rank there; then its position
+    int eq[SPT], tot;
+    sum = 0;
+#pragma unroll
+    for (int u = 0; u < SPT; ++u) {
+      eq[u] = SPT * tid + u < ntk ? (int)L.kept[TK_MAX_SLICES + SPT * tid + u] : 0;
+      sum += eq[u];
+    }
+    int before = block_excl_scan<TKT>(sum, L.W, &tot);
+#pragma unroll
+    for (int u = 0; u < SPT; ++u) {
+      const int take = min(max(need - before, 0), eq[u]);
+      if (SPT * tid + u < ntk) L.kept[SPT * tid + u] += (uint32_t)take;
+      if (before < need && before + eq[u] >= need) {
+        L.cut = SPT * tid + u;
+        L.rank = need - before;
+      }
+      before += eq[u];
+    }
+    __syncthreads();
+    const int sc = L.cut;
+    auto mark = [&](uint64_t c) {
+      const int pos = (int)(uint32_t)c;
+      if ((uint32_t)(c >> 32) == T && pos / TKS == sc)
+        atomicOr(reinterpret_cast<unsigned long long*>(&L.bits[(pos % TKS) / 64]), 1ull << (pos % 64));
+    };
+    if (in_lds) {
+      for (int f = tid; f < m; f += TKT) mark(L.cand[f]);
+    } else if constexpr (GROUPED) {
+      if (wave == 0) slice_cands(sc, mark);
+    }
+    __syncthreads();
+    if (wave == 0) {  // the rank-th set bit: one word per lane
+      uint64_t w = lane < TKS / 64 ? L.bits[lane] : 0ull;
+      const int n = __popcll(w), incl = wave_incl_scan(n);
+      int r = L.rank - (incl - n);
+      if (r >= 1 && r <= n) {
+        for (; r > 1; --r) w &= w - 1ull;
+        L.P = sc * TKS + 64 * lane + (int)__builtin_ctzll(w);
+      }
+    }
+    __syncthreads();
+  }
   int kept[SPT], tot;
   sum = 0;
 #pragma unroll
   for (int u = 0; u < SPT; ++u) {
     const int i = SPT * tid + u;
     kept[u] = 0;
-    if (i < ntk) kept[u] = L.in_bin[i] + (int)(uint32_t)cn[u];
+    if (i < ntk) kept[u] = (int)L.kept[i] + (int)(uint32_t)cn[u];
     sum += kept[u];
   }
   int ob = block_excl_scan<TKT>(sum, L.W, &tot);
@@ -1293,7 +1485,7 @@ __device__ __forceinline__ void tk_finish(TkLds& L, int head, int k, int ntk, in
   }
   if (tid == 0) {
     sel[2 * head] = (int)T;
-    sel[2 * head + 1] = P;
+    sel[2 * head + 1] = L.P;
   }
 }
 
@@ -1329,35 +1521,42 @@ __global__ void __launch_bounds__(TKT) k_tk_cand(const float* __restrict__ score
   uint32_t bin, above;  // every wave finds the same
   wave_find_bin<TK_HBINS>(L.hist, k, &bin, &above);
   const int B = (int)bin;
-  // the slice's candidates, counted and placed by ballots (their order does not matter)
-  int n_gt = 0, n_c = 0;
-  uint64_t in[TKPT];
-#pragma unroll
-  for (int u = 0; u < TKPT; ++u) {
-    const int b = key_bin(key[u]);
-    n_gt += __popcll(__ballot(valid[u] && b > B));
-    in[u] = __ballot(valid[u] && b == B);
-    n_c += __popcll(in[u]);
-  }
-  if (lane == 0) L.W[wave] = n_gt | (n_c << 16);  // at most 512 of each
-  __syncthreads();
-  int before = 0, tot = 0;
-#pragma unroll
-  for (int w = 0; w < TKT / 64; ++w) {
-    const int t = L.W[w];
-    before += w < wave ? t >> 16 : 0;
-    tot += t;
-  }
-  uint64_t* c = cand + ((size_t)head * ntk + sl) * TKS + before;
+  uint64_t* c = cand + ((size_t)head * ntk + sl) * TK_STRIDE;
   const int j0 = sl * TKS + TKPT * threadIdx.x;
+  const int n_bin = (int)L.hist[B];
+  const bool grouped = n_bin > TK_CAND_LDS;  // the same for every slice
+  if (__builtin_expect(grouped, 0)) {
+    tk_post_grouped(L, key, n, B, j0, cnt + (size_t)head * ntk + sl, c);
+  } else {
+    // the slice's candidates, counted and placed by ballots (their order does not matter)
+    int n_gt = 0, n_c = 0;
+    uint64_t in[TKPT];
 #pragma unroll
-  for (int u = 0; u < TKPT; ++u) {
-    if ((in[u] >> lane) & 1)
-      st_agent_u64(c + __popcll(in[u] & ((1ull << lane) - 1ull)), ((uint64_t)key[u] << 32) | (uint32_t)(j0 + u));
-    c += __popcll(in[u]);
+    for (int u = 0; u < TKPT; ++u) {
+      const int b = key_bin(key[u]);
+      n_gt += __popcll(__ballot(valid[u] && b > B));
+      in[u] = __ballot(valid[u] && b == B);
+      n_c += __popcll(in[u]);
+    }
+    if (lane == 0) L.W[wave] = n_gt | (n_c << 16);  // at most 512 of each
+    __syncthreads();
+    int before = 0, tot = 0;
+#pragma unroll
+    for (int w = 0; w < TKT / 64; ++w) {
+      const int t = L.W[w];
+      before += w < wave ? t >> 16 : 0;
+      tot += t;
+    }
+    c += before;
+#pragma unroll
+    for (int u = 0; u < TKPT; ++u) {
+      if ((in[u] >> lane) & 1)
+        st_agent_u64(c + __popcll(in[u] & ((1ull << lane) - 1ull)), ((uint64_t)key[u] << 32) | (uint32_t)(j0 + u));
+      c += __popcll(in[u]);
+    }
+    if (threadIdx.x == 0)
+      st_agent_u64(cnt + (size_t)head * ntk + sl, (uint64_t)(tot & 0xFFFF) | ((uint64_t)(tot >> 16) << 32));
   }
-  if (threadIdx.x == 0)
-    st_agent_u64(cnt + (size_t)head * ntk + sl, (uint64_t)(tot & 0xFFFF) | ((uint64_t)(tot >> 16) << 32));
   // count in; the last workgroup of the head selects
   stores_complete();
   __syncthreads();
@@ -1366,7 +1565,8 @@ __global__ void __launch_bounds__(TKT) k_tk_cand(const float* __restrict__ score
   if (!L.last) return;
   if (threadIdx.x == 0) __hip_atomic_store(arr + head, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   loads_after_count();
-  tk_finish(L, head, k, ntk, B, (int)above, cnt, cand, sel, off);
+  if (__builtin_expect(grouped, 0)) tk_finish<true>(L, head, k, ntk, B, (int)above, n_bin, cnt, cand, sel, off);
+  else tk_finish<false>(L, head, k, ntk, B, (int)above, n_bin, cnt, cand, sel, off);
 }
 
 // COV: the same workgroup then adds the covariance and sums of its slice's kept rows

@@ -119,7 +119,7 @@ mkv::CompressArgs compress_layout(const mkv_compress_params* p, void* ws, size_t
   a.tk_cnt = c.take<uint64_t>(H * a.ntk * sizeof(uint64_t));
   a.tk_sel = c.take<int32_t>(H * 2 * sizeof(int32_t));
   a.tk_off = c.take<int32_t>(H * a.ntk * sizeof(int32_t));
-  a.tk_cand = c.take<uint64_t>(H * a.ntk * 2048 * sizeof(uint64_t));
+  a.tk_cand = c.take<uint64_t>(H * a.ntk * mkv::kTkSliceWords * sizeof(uint64_t));
   a.spart = c.take<float>(H * a.nslot * D * D * sizeof(float));
   a.svkpart = c.take<float>(H * a.nslot * 2 * D * sizeof(float));
   a.s0 = c.take<float>(H * D * D * sizeof(float));
@@ -133,7 +133,7 @@ mkv::CompressArgs compress_layout(const mkv_compress_params* p, void* ws, size_t
     a.tk_cnt_g = c.take<uint64_t>(Bs * a.ntk_g * sizeof(uint64_t));
     a.tk_sel_g = c.take<int32_t>(Bs * 2 * sizeof(int32_t));
     a.tk_off_g = c.take<int32_t>(Bs * a.ntk_g * sizeof(int32_t));
-    a.tk_cand_g = c.take<uint64_t>(Bs * a.ntk_g * 2048 * sizeof(uint64_t));
+    a.tk_cand_g = c.take<uint64_t>(Bs * a.ntk_g * mkv::kTkSliceWords * sizeof(uint64_t));
   }
   *total = c.off;
   return a;

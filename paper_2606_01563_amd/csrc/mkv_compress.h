@@ -12,6 +12,8 @@ namespace mkv {
 constexpr int kRowsMaxTiles = 64;
 constexpr int kMassMaxTiles = 32;
 constexpr int kResMaxTiles = 32;
+// Top-k: 8-byte words of a slice's hand-over, 2048 candidates and 512 16-bit offsets.
+constexpr int kTkSliceWords = 2048 + 128;
 
 struct CompressArgs {
   const void* q_win;        // [B, Hq, w, D]
@@ -40,7 +42,8 @@ struct CompressArgs {
   int32_t* tk_arr;          // [H]               top-k: slices arrived, zero between launches
   uint64_t* tk_cnt;         // [H, ntk]          top-k: per slice, keys above the k-th key's
                             //                   bin, and (high half) in it
-  uint64_t* tk_cand;        // [H, ntk, 2048]    top-k: (key, position) of the keys in the bin
+  uint64_t* tk_cand;        // [H, ntk, kTkSliceWords]  top-k: (key, position) of the keys in the bin,
+                            //                   and their grouping in a large one
   int32_t* tk_sel;          // [H, 2]            top-k: the k-th key, the last equal position kept
   int32_t* tk_off;          // [H, ntk]          top-k: per slice, output offset
   float* spart;             // [H, nslot, D, D]  covariance partials (after the row-statistics
@@ -71,7 +74,7 @@ struct CompressArgs {
   uint32_t* tk_hs;          // [B, 2048] key histogram of abar over the layer
   int32_t* tk_arr_g;        // [B], and the buffers of that selection:
   uint64_t* tk_cnt_g;       // [B, ntk_g]
-  uint64_t* tk_cand_g;      // [B, ntk_g, 2048]
+  uint64_t* tk_cand_g;      // [B, ntk_g, kTkSliceWords]
   int32_t* tk_sel_g;        // [B, 2]
   int32_t* tk_off_g;        // [B, ntk_g]
   int ntk_g;                // slices of the layer-wide selection

@@ -506,9 +506,9 @@ def test_compress_and_decode_are_bit_deterministic():
 
 @pytest.mark.parametrize("log2_v,mi_rounds", [(-60, 0), (-60, 1), (40, 0)])
 def test_selection_with_scores_outside_the_histogram(log2_v, mi_rounds):
-    """Values scaled so that every score falls into an end bin of the key histogram (below
-    2^-28, above 2^4): the selection then refines whole keys over all candidates, three
-    slices of them."""
+    """Values scaled so that every score falls outside the fine bins of the key histogram
+    (below 2^-26, above 2^2), into bins of an octave: two or three of them hold all
+    candidates, three slices."""
     wl, cpu, gpu = layer("tiny_fp32_n2048", steps=1, dtype=torch.bfloat16, head_dim=128, ctx_len=5000,
                          n_q_heads=4, n_kv_heads=2, window=16, budgets=(333,))
     for x in (cpu, gpu):
@@ -518,12 +518,77 @@ def test_selection_with_scores_outside_the_histogram(log2_v, mi_rounds):
         announce(f"v * 2^{log2_v}: {P.check_compress_head(cpu, out, 0, h, 333, mi_rounds=mi_rounds)}")
 
 
+def _kept_by_own_scores(score, k):
+    """Positions of the k largest, the lower position among equal ones, ascending."""
+    return np.sort(np.lexsort((np.arange(score.size), -score.astype(np.float64)))[:k])
+
+
+@pytest.mark.parametrize("values", ["octave", "fine bin", "three values", "mostly zero", "mixed"])
+@pytest.mark.parametrize("ctx_len", [9996, 140036])
+def test_selection_over_large_bins(ctx_len, values):
+    """More candidates in the k-th key's histogram bin than the selection stages in LDS, over 5
+    and 69 slices: equal window masses times chosen value norms.  Bins of distinct keys (an
+    octave's, a fine one: the sub-bin fits), of few distinct keys (the sub-bin does not fit),
+    zeros, and a wide mixture; k at both ends and in the middle.  The kept set is exactly the
+    top-k of the call's own scores."""
+    wl, cpu, gpu = layer("tiny_fp32_n2048", steps=1, ctx_len=ctx_len, budgets=(200,))
+    n_s, c_hi = 4, ctx_len - wl.window
+    n_c = c_hi - n_s
+    rng = np.random.default_rng(5)
+    x = {"octave": lambda: 2.0 ** -35 * (1.0 + rng.random(n_c)),
+         "fine bin": lambda: 1.0 + rng.random(n_c) / 256,
+         "three values": lambda: 1.0 + rng.integers(0, 3, n_c) * 2.0 ** -22,
+         "mostly zero": lambda: np.where(rng.random(n_c) < 0.7, 0.0, 2.0 ** rng.uniform(-80, 0, n_c)),
+         "mixed": lambda: np.where(rng.random(n_c) < 0.6, 3.0, 2.0 ** rng.uniform(-60, 20, n_c))}[values]()
+    k, v = cpu["k"].clone(), cpu["v"].clone()
+    k[0, 0, n_s:c_hi] = k[0, 0, 5]
+    v[0, 0, n_s:c_hi] = 0.0
+    v[0, 0, n_s:c_hi, 7] = torch.from_numpy(x.astype(np.float32))
+    gpu["k"], gpu["v"] = k.cuda(), v.cuda()
+    for k_keep in (1, 150, n_c // 3, n_c // 2 + 7, n_c - 5):
+        budget = k_keep + n_s + wl.window
+        announce(f"{values}, {n_c} candidates, k {k_keep}")
+        out = P.run_compress(gpu, budget, cap=budget, mi_rounds=0, n_sink=n_s)
+        score = out.score0[0, 0].cpu().numpy()
+        expect = _kept_by_own_scores(score, k_keep) + n_s
+        np.testing.assert_array_equal(out.kept0[0, 0, :k_keep].cpu().numpy(), expect)
+        np.testing.assert_array_equal(out.idx[0, 0, n_s:n_s + k_keep].cpu().numpy(), expect)
+
+
+@pytest.mark.parametrize("ctx_len", [9996, 34036])
+@pytest.mark.parametrize("same_keys", [True, False])
+def test_head_budgets_over_large_bins(ctx_len, same_keys):
+    """The layer-wide selection of the head-adaptive budgets with equal masses in every head
+    (all candidates in a bin or two), and with sharp attention: each head's share is what the
+    call's own masses give."""
+    wl, cpu, gpu = layer("tiny_fp32_n2048", steps=1, ctx_len=ctx_len, n_q_heads=8, n_kv_heads=4,
+                         dtype=torch.bfloat16, head_dim=128, budgets=(200,))
+    n_s, c_hi = 4, ctx_len - wl.window
+    n_c = c_hi - n_s
+    if same_keys:
+        gpu["k"][0, :, n_s:c_hi] = gpu["k"][0, :, 5:6]
+    else:
+        gpu["q_win"] = gpu["q_win"] * 6
+    for k_keep in (1, 150, n_c // 3):
+        budget = k_keep + n_s + wl.window
+        rows = mk.compress_rows(ctx_len, 4, budget, wl.window, n_s, True)
+        out = P.run_compress(gpu, budget, cap=rows, mi_rounds=-1, n_sink=n_s, adaptive=True)
+        top = _kept_by_own_scores(out.abar[0].cpu().numpy().reshape(-1), 4 * k_keep)
+        expect = np.bincount(top // n_c, minlength=4)
+        announce(f"{n_c} candidates per head, k {k_keep}: shares {expect}")
+        np.testing.assert_array_equal(out.lens[0].cpu().numpy() - n_s - wl.window, expect)
+        for h in range(4):
+            np.testing.assert_array_equal(
+                out.idx[0, h, n_s:n_s + expect[h]].cpu().numpy(),
+                _kept_by_own_scores(out.abar[0, h].cpu().numpy(), expect[h]) + n_s)
+
+
 @pytest.mark.parametrize("ctx_len", [12000, 33000])
 @pytest.mark.parametrize("mi_rounds", [-1, 0])
 def test_selection_with_all_scores_equal_keeps_the_lowest_positions(ctx_len, mi_rounds):
     """Every candidate score equal (identical candidate keys give equal window masses;
     zero values give zero scores): the kept set is the k lowest candidate positions, the
-    tie rule of the selection.  Both sizes put more keys in the k-th key's bin than the
+    tie rule of the selection.  Both sizes put more keys in the k-th key's sub-bin than the
     refinement stages in LDS (it then reads them from global memory), over 6 and 17
     slices of 2048 positions."""
     wl, cpu, gpu = layer("tiny_fp32_n2048", steps=1, ctx_len=ctx_len, budgets=(200,))
