@@ -998,9 +998,11 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_decode_group(Decod
   // count in; the last workgroup of the head merges it
   stores_complete();
   __syncthreads();
-  const int arr_shift = 16 * (head & 1);  // two heads per counter word
+  // a counter word per head, from kGroupWords heads on one per two (16 bits each)
+  uint32_t* const arr = reinterpret_cast<uint32_t*>(a.cnt) + (head < kGroupWords ? head : head - kGroupWords);
+  const int arr_shift = head < kGroupWords ? 0 : 16;
   if (threadIdx.x == 0) {
-    const uint32_t prior = atomicAdd(a.group_cnt + (head >> 1), 1u << arr_shift);
+    const uint32_t prior = atomicAdd(arr, 1u << arr_shift);
     s_last = (int)((prior >> arr_shift) & 0xFFFFu) == (n_sq > 0) + a.nsplit - 1;
   }
   __syncthreads();
@@ -1065,7 +1067,8 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_decode_group(Decod
   }
   if (threadIdx.x == 0) {
     // every other workgroup of the head has counted itself in, and so has read lens
-    atomicAnd(a.group_cnt + (head >> 1), 0xFFFF0000u >> arr_shift);
+    if (a.n_heads <= kGroupWords) __hip_atomic_store(arr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else atomicAnd(arr, 0xFFFF0000u >> arr_shift);
   }
   __syncthreads();  // every wave has read lens
   if (threadIdx.x == 0 && hl.can_append) a.lens[head] = hl.old_len + 1;

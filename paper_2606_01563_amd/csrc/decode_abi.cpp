@@ -141,7 +141,6 @@ mkv::DecodeArgs decode_layout(const mkv_decode_params* p, void* ws, size_t* tota
   // arrival counter per head) are zero-filled by the caller before first use; every call
   // leaves the counters at zero.
   a.flag = c.take<int32_t>(sizeof(int32_t));
-  a.group_cnt = a.flag ? reinterpret_cast<uint32_t*>(a.flag) + 1 : nullptr;
   a.cnt = c.take<int32_t>(std::max<size_t>(cnt_slots, H) * sizeof(int32_t));
   auto take_parts = [&](size_t n) {
     a.part_o = c.take<float>(H * n * G * D * sizeof(float));
@@ -153,6 +152,7 @@ mkv::DecodeArgs decode_layout(const mkv_decode_params* p, void* ws, size_t* tota
   if (a.shape == kDecodeGroup) {
     // The group launch's few partials at the end of the reservation: away from the leading
     // bytes, where a call with more heads on the same workspace has its counters.
+    if (a.flag) a.cnt = a.flag + 1;
     const size_t end = c.off;
     c.off = first;
     take_parts(a.nsplit);
