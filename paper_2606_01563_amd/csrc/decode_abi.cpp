@@ -34,20 +34,63 @@ constexpr int64_t kMaxDecodeWaves = 1 << 24;  // decode grid limit (single-wave 
 //   96 heads   450 rows 12.1 / 13.1 / 15.4   1020 rows 19.5 / 15.0 / 19.2
 //   128 heads  600 rows 14.2 / 15.8 / 18.2   1020 rows 19.6 / 17.0 / 20.0
 //   192 heads  600 rows 14.4 / 17.3 / 23.6   1020 rows 19.7 / 19.9 / 31.1
+// Other types, head dims, groups and orders (G q heads; one workgroup / slices / groups):
+//   bf16 d 64, G 4      8 heads  300 rows  5.8 /  7.7 /  7.3    96 heads 640 rows  8.7 / 10.4 /  -
+//   bf16 d 64, G 16    64 heads  384 rows  9.2 / 20.7 / 12.6
+//   bf16 d 128, G 8    64 heads  257 rows 10.6 / 16.7 / 11.3    64 heads 384 rows 12.4 / 20.0 / 12.0
+//   bf16 d 128, G 16   64 heads  300 rows 13.6 / 25.9 / 14.6
+//   bf16 d 128, G 1     2 heads  450 rows 11.2 /  8.6 /  8.7    96 heads 640 rows 14.2 / 13.0 /  -
+//   bf16, order 0       8 heads  300 rows  7.7 /  8.7 /  9.1
+//   bf16, raw summary  32 heads  257 rows 11.0 / 10.5 / 10.1    96 heads 640 rows 17.2 / 15.3 /  -
+//   fp32 d 128, G 4    64 heads  300 rows 20.9 / 17.0 / 13.5     2 heads 450 rows 26.0 / 11.1 / 12.2
+//                      64 heads  450 rows 27.7 / 18.0 / 18.7    32 heads 1500 rows  -  / 24.4 / 20.2
+//                      32 heads 4096 rows   -  / 37.0 / 39.1    96 heads 640 rows 34.1 / 23.9 /  -
+//                     160 heads  640 rows 34.8 / 32.4 /  -     256 heads 640 rows 40.4 / 46.8 /  -
+//   fp32 d 128, G 8     8 heads  640 rows   -  / 18.5 / 15.2    32 heads 1500 rows  -  / 30.4 / 22.6
+//   fp32 d 128, G 16  128 heads  512 rows 33.8 / 39.2 /  -
+// (in fp32 a block's products take a wave several times as long: one workgroup per head or
+// two blocks per wave of a group lose to slices earlier; at d = 64, or without the summary's
+// product, a short cache is too little work to hand over.)
 // Up to 256 rows every head runs in one workgroup.  Longer caches of few heads: the
 // smallest group length (a multiple of 128 rows) that keeps the launch at kGroupWgs token
 // workgroups and, from 8 waves each (one workgroup per CU), with the heads' S_tilde q
 // workgroups at the CUs, so that each starts at once; longer groups than kGroupMaxLen lose
 // to slices where the lengths differ, except with so few heads that slices are many per
-// head.  Otherwise one workgroup per head, which needs no hand-off, while the caches are
-// short for how far the heads fill the CUs; else slices.
+// head.  groups_pay() leaves out what the lines above show.  Otherwise one workgroup per
+// head, which needs no hand-off, while the caches are short for how far the heads fill the
+// CUs (fused_max_len()); else slices.
 constexpr int kCUs = 256;
 constexpr int kFusedMaxLen = 256;
 constexpr int kFusedMaxLenMany = 384;   // any number of heads
-constexpr int kFusedMaxLenHalf = 640;   // up to kCUs / 2 heads
-constexpr int kFusedMaxLenFull = 1024;  // kCUs / 2 to kCUs heads
 constexpr int kGroupWgs = 192, kGroupMaxLen = 384;
 constexpr int kGroupVeryFewHeads = 32, kGroupMaxLenVeryFew = 768;
+
+bool groups_pay(const mkv_decode_params* p, int64_t heads, int group_len) {
+  const bool f32 = p->dtype == MKV_F32, d64 = p->head_dim == 64;
+  const int rows = p->max_len, G = p->n_q_heads / p->n_kv_heads;
+  if (rows <= kFusedMaxLenMany) {  // against one workgroup per head
+    if (f32) return d64 ? G <= 8 && heads <= 64 && rows > 288 : heads <= 64 || rows > 288;
+    const bool raw = p->summary == 0 || p->summary == 3;
+    return !d64 && p->order >= 1 && G <= 8 && (raw || (heads <= 64 && rows > 288));
+  }
+  if (!f32 || G > 4) return true;  // against slices
+  if (group_len == 128) return heads >= 8 || rows > 640;
+  return d64 ? rows >= 640 : heads <= 64 && rows > 640 && group_len <= 512;
+}
+
+// Longest cache for which one workgroup per head beats slices (with too many heads, or too
+// few rows, for groups).
+int fused_max_len(const mkv_decode_params* p, int64_t heads) {
+  const bool f32 = p->dtype == MKV_F32, d64 = p->head_dim == 64, wide = p->n_q_heads / p->n_kv_heads > 4;
+  if (heads > kCUs || 3 * heads <= kCUs) return kFusedMaxLenMany;
+  if (heads > 160) return 1024;
+  if (f32 && !d64) {
+    const bool wider = p->n_q_heads / p->n_kv_heads > 8;
+    return heads > 128 ? (wider ? 1024 : 512) : (wider ? 512 : kFusedMaxLenMany);
+  }
+  if (heads > 128) return 1024;
+  return heads == 128 || wide || (d64 && !f32) ? 640 : 512;
+}
 static_assert(kGroupWgs / 2 <= mkv::kMaxGroupHeads, "at least two groups per head");
 
 // ----------------------------------------------------------------------- decode
@@ -72,6 +115,7 @@ mkv::DecodeShape decode_shape(const mkv_decode_params* p, int* split_len, int* n
       const int n = ceil_div(p->max_len, gl);
       if (n > 1 && n <= mkv::kMaxGroups && heads * n <= kGroupWgs &&
           (gl < mkv::kGroupWideLen || heads * (n + 1) <= kCUs)) {
+        if (!groups_pay(p, heads, gl)) break;
         *split_len = gl;
         *nsplit = n;
         return mkv::kDecodeGroup;
@@ -80,8 +124,7 @@ mkv::DecodeShape decode_shape(const mkv_decode_params* p, int* split_len, int* n
   }
   slice_split(p, split_len, nsplit);
   if (p->n_split == 1) return mkv::kDecodeFused;
-  const int fused_max = heads > kCUs ? kFusedMaxLenMany : heads > kCUs / 2 ? kFusedMaxLenFull : kFusedMaxLenHalf;
-  if (p->n_split == 0 && p->max_len <= fused_max) return mkv::kDecodeFused;
+  if (p->n_split == 0 && p->max_len <= fused_max_len(p, heads)) return mkv::kDecodeFused;
   return mkv::kDecodeSlices;
 }
 

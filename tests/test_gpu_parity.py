@@ -33,6 +33,34 @@ def announce(msg):
     print(f"[parity] {msg}", flush=True)
 
 
+def _decode_state(Hkv, G, d, rows, seed, batch=1, dtype=torch.bfloat16):
+    """Random caches of `rows` rows with summaries: (q, k, v, lens, n_e, s_k, s_v, S)."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    r = lambda *s: torch.randn(*s, device="cuda", generator=g)
+    i = lambda lo, hi: torch.randint(lo, hi, (batch, Hkv), device="cuda", generator=g, dtype=torch.int32)
+    kc, vc = r(batch, Hkv, rows, d).to(dtype), r(batch, Hkv, rows, d).to(dtype)
+    return (r(batch, Hkv * G, d).to(dtype), kc, vc, i(rows // 2, rows), i(0, 900),
+            r(batch, Hkv, d) * 30, r(batch, Hkv, d) * 30, r(batch, Hkv, d, d) * 50)
+
+
+def launch_shape(dtype, d, G, heads, rows, order=1, summary=0):
+    """The automatic launch shape of a decode call, from where it writes in its workspace:
+    slices right after the leading bytes, token groups at the end only, one workgroup per
+    head nowhere."""
+    args = _decode_state(1, G, d, rows, 1, batch=heads, dtype=dtype)
+    args[3].fill_(rows)
+    if summary == 1:
+        args = (*args[:7], mk.momentkv_prepare_summary(*args[4:8], dtype=dtype))
+    p = mk.decode_params(args[0], args[1], max_len=rows, order=order, summary=summary)
+    ws = torch.full((mk.momentkv_decode_workspace_bytes(p),), 0xFF, dtype=torch.uint8, device="cuda")
+    zero = mk.momentkv_decode_workspace_zero_bytes(p)
+    assert mk.momentkv_decode_attn(*args, order=order, summary=summary, workspace=ws)[3] is ws
+    assert int(ws[:zero].sum()) == 0
+    if bool((ws[zero:zero + 64] != 0xFF).any()):
+        return "slices"
+    return "groups" if bool((ws[zero:] != 0xFF).any()) else "one"
+
+
 # ---------------------------------------------------------------- tiny fp32 workload
 def test_tiny_fp32_compress_and_decode():
     wl, cpu, gpu = layer("tiny_fp32_n2048", steps=16)
@@ -197,21 +225,53 @@ def test_decode_single_launch_block_rounds(d, dtype, cap):
     P.run_decode_steps(gpu, out, 3, n_split=1, lens0=lens0, summary=1)
 
 
-@pytest.mark.parametrize("cap,append", [(300, True), (300, False), (1500, True)])
+@pytest.mark.parametrize("d,cap,append", [(128, 300, True), (128, 300, False), (64, 450, True),
+                                          (64, 450, False), (64, 1500, True), (128, 1500, True)])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-@pytest.mark.parametrize("d", [64, 128])
 def test_decode_token_groups(d, dtype, cap, append):
     """Few heads and more than 256 rows (automatic: token groups of 128 rows merged by the
     last workgroup of the head): lengths on both sides of the group and block boundaries,
     an empty head, appends landing on a group's first row, up to 12 groups."""
     L = cap - 3
     wl, cpu, gpu = layer("tiny_fp32_n2048", steps=3, dtype=dtype, head_dim=d, ctx_len=max(1000, cap + 300),
-                         batch=3, n_q_heads=6, n_kv_heads=2, window=16, budgets=(L,))
+                         batch=5, n_q_heads=6, n_kv_heads=2, window=16, budgets=(L,))
+    assert launch_shape(dtype, d, 3, 10, cap, summary=int(append)) == "groups"
     out = P.run_compress(gpu, L, cap=cap)
-    lens0 = ([[0, 127], [128, 160], [255, 297]] if cap == 300
-             else [[0, 1], [640, 1407], [1279, 1497]])
+    lens0 = {300: [[0, 127], [128, 160], [255, 297], [1, 256], [257, 31]],
+             450: [[0, 127], [128, 383], [384, 447], [1, 256], [385, 31]],
+             1500: [[0, 1], [640, 1407], [1279, 1497], [1408, 32], [1280, 128]]}[cap]
     announce(f"token groups d={d} {dtype} cap={cap} lengths {lens0} append={append}")
     P.run_decode_steps(gpu, out, 3, n_split=0, append=append, lens0=lens0, summary=int(append))
+
+
+@pytest.mark.parametrize("G", [4, 8, 16])
+@pytest.mark.parametrize("d", [64, 128])
+def test_decode_wide_token_groups(d, G):
+    """Token groups of 256 rows (8-wave workgroups, bf16; 2 heads of 2100 rows): empty groups
+    past a short head, ragged last blocks, an empty head, appends on a group's first row."""
+    cap = 2100
+    wl, cpu, gpu = layer("tiny_fp32_n2048", steps=2, dtype=torch.bfloat16, head_dim=d, ctx_len=2500,
+                         batch=2, n_q_heads=G, n_kv_heads=1, window=16, budgets=(cap - 2,))
+    assert launch_shape(torch.bfloat16, d, G, 2, cap, summary=1) == "groups"
+    out = P.run_compress(gpu, cap - 2, cap=cap)
+    for lens0 in ([[0], [2098]], [[255], [1793]], [[1023], [1]]):
+        announce(f"256-row groups d={d} G={G} lengths {lens0}")
+        P.run_decode_steps(gpu, out, 2, lens0=lens0, summary=1)
+
+
+@pytest.mark.parametrize("n_split", [20, 70])
+@pytest.mark.parametrize("dtype,d,G", [(torch.bfloat16, 128, 4), (torch.bfloat16, 64, 1),
+                                       (torch.float32, 128, 2)])
+def test_decode_many_slices(dtype, d, G, n_split):
+    """More slices per head than the merging wave takes at once (16): 19 of 128 rows, 68 of 32;
+    lengths 0, 1, within a slice, and full."""
+    cap = 2176
+    wl, cpu, gpu = layer("tiny_fp32_n2048", steps=2, dtype=dtype, head_dim=d, ctx_len=2500, batch=2,
+                         n_q_heads=2 * G, n_kv_heads=2, window=16, budgets=(cap - 2,))
+    out = P.run_compress(gpu, cap - 2, cap=cap)
+    lens0 = [[0, cap - 2], [1, 1237]]
+    announce(f"{dtype} d={d} G={G} n_split={n_split} lengths {lens0}")
+    P.run_decode_steps(gpu, out, 2, n_split=n_split, lens0=lens0, summary=1)
 
 
 @pytest.mark.parametrize("G", [8, 16])
@@ -244,14 +304,39 @@ def test_decode_token_groups_repeat_bit_exact(G):
     assert torch.equal(na, ref)
 
 
-def _decode_state(Hkv, G, d, rows, seed, batch=1):
-    """Random caches of `rows` rows with summaries: (q, k, v, lens, n_e, s_k, s_v, S)."""
-    g = torch.Generator(device="cuda").manual_seed(seed)
-    r = lambda *s: torch.randn(*s, device="cuda", generator=g)
-    i = lambda lo, hi: torch.randint(lo, hi, (batch, Hkv), device="cuda", generator=g, dtype=torch.int32)
-    kc, vc = r(batch, Hkv, rows, d).to(torch.bfloat16), r(batch, Hkv, rows, d).to(torch.bfloat16)
-    return (r(batch, Hkv * G, d).to(torch.bfloat16), kc, vc, i(rows // 2, rows), i(0, 900),
-            r(batch, Hkv, d) * 30, r(batch, Hkv, d) * 30, r(batch, Hkv, d, d) * 50)
+SHAPE_LINES = {  # (dtype, d, G, order, summary): [(heads, rows, shape)]
+    ("bf16", 128, 4, 1, 1): [(8, 256, "one"), (8, 288, "one"), (8, 289, "groups"), (64, 384, "groups"),
+                             (65, 384, "one"), (64, 1152, "groups"), (64, 1153, "slices"),
+                             (2, 385, "groups"), (85, 768, "groups"), (86, 512, "one"), (86, 513, "slices"),
+                             (128, 640, "one"), (128, 641, "slices"), (160, 1024, "one"),
+                             (256, 1025, "slices"), (257, 384, "one"), (257, 385, "slices")],
+    ("bf16", 128, 4, 1, 0): [(8, 256, "one"), (8, 257, "groups"), (80, 384, "groups"), (96, 384, "one")],
+    ("bf16", 128, 8, 1, 1): [(8, 384, "groups"), (96, 640, "one"), (96, 641, "slices")],
+    ("bf16", 128, 16, 1, 1): [(8, 384, "one"), (2, 385, "groups")],
+    ("bf16", 128, 4, 0, 1): [(8, 384, "one"), (8, 385, "groups")],
+    ("bf16", 64, 4, 1, 1): [(8, 384, "one"), (8, 385, "groups"), (96, 640, "one"), (96, 641, "slices")],
+    ("fp32", 128, 4, 1, 0): [(2, 256, "one"), (2, 257, "groups"), (65, 288, "one"), (65, 289, "groups"),
+                             (7, 640, "slices"), (7, 641, "groups"), (8, 385, "groups"),
+                             (48, 512, "groups"), (48, 640, "slices"), (48, 641, "groups"),
+                             (65, 641, "slices"), (24, 4096, "groups"), (32, 3073, "slices"),
+                             (128, 384, "one"), (128, 385, "slices"), (160, 512, "one"),
+                             (160, 513, "slices"), (161, 1024, "one")],
+    ("fp32", 128, 4, 0, 0): [(8, 384, "groups")],
+    ("fp32", 128, 16, 1, 0): [(2, 450, "groups"), (128, 512, "one"), (128, 513, "slices"), (160, 1024, "one")],
+    ("fp32", 64, 4, 1, 0): [(8, 288, "one"), (8, 289, "groups"), (48, 639, "slices"), (48, 640, "groups"),
+                            (96, 512, "one"), (96, 513, "slices"), (160, 1024, "one")],
+    ("fp32", 64, 16, 1, 0): [(8, 384, "one"), (96, 640, "one")],
+}
+
+
+@pytest.mark.parametrize("key", list(SHAPE_LINES), ids=lambda k: "-".join(map(str, k)))
+def test_decode_launch_shape_lines(key):
+    """The automatic launch shape on both sides of its lines in rows and heads."""
+    dtype, d, G, order, summary = key
+    for heads, rows, shape in SHAPE_LINES[key]:
+        announce(f"{key} heads {heads} rows {rows}: {shape}")
+        assert launch_shape(torch.float32 if dtype == "fp32" else torch.bfloat16, d, G, heads, rows,
+                            order, summary) == shape, (heads, rows)
 
 
 @pytest.mark.parametrize("few", ["groups", "slices", "evict"])
@@ -728,8 +813,8 @@ def test_half_precision_summary_error_against_fp32_summary():
 def test_qwen_stack_layer_full_size_sampled_heads(budget):
     """One 32K-context layer of the Qwen3-4B-shaped stack at every budget of the stack
     workload, checked on two sampled KV heads; then decode in the benchmark's launch shape
-    (capacity budget + 128, so the single launch up to budget 256 and the split launch from
-    512): 8 steps at 256 and 512 with the prepared summary, 2 steps otherwise."""
+    (8 heads, capacity budget + 128: the single launch at budget 128, token groups from 256):
+    8 steps at 256 and 512 with the prepared summary, 2 steps otherwise."""
     steps = 8 if budget in (256, 512) else 2
     wl, cpu, gpu = layer("qwen3_4b_stack_n32768", layer_idx=3, steps=steps)
     announce(f"{wl.name} L={budget}")
