@@ -26,8 +26,8 @@ namespace {
 // updates and then attends to the new cache itself (a second read of a short cache,
 // mostly from L2); a fused workgroup holds one head's summary and V tiles alone on its
 // CU, which there costs more than that second read.
-// Workspace: the flag first, then the score records and the per-block running maxima;
-// fused: then the heads' partial states.
+// Workspace: the flag first, then the score records and the per-block running maxima, then
+// the heads' partial states (fused).
 constexpr int kCUs = 256;
 // max_len from which the one-read shape runs.  Measured per call (d = 128, G = 4), short
 // against one-read shape, us:
@@ -66,10 +66,10 @@ mkv::EvictArgs evict_layout(const mkv_decode_params* p, int32_t budget, void* ws
   const size_t H = e.n_heads, G = e.G, D = p->head_dim;
   Carver c;
   c.base = static_cast<char*>(ws);
+  const int64_t want = p->n_split > 0 ? (int64_t)p->n_split * e.n_heads : kCUs;
   if (e.fused) {
     const int64_t T = (int64_t)e.n_heads * e.hblocks;
-    int64_t nwg = p->n_split > 0 ? (int64_t)p->n_split * e.n_heads : kCUs;
-    nwg = std::max<int64_t>(1, std::min(nwg, T));
+    int64_t nwg = std::max<int64_t>(1, std::min(want, T));
     auto slots = [&](int64_t n) {
       const int64_t per = std::max<int64_t>(1, T / n);  // the fewest blocks a workgroup takes
       return std::min<int64_t>(n, (e.hblocks + per - 1) / per + 1);
@@ -81,10 +81,14 @@ mkv::EvictArgs evict_layout(const mkv_decode_params* p, int32_t budget, void* ws
   e.flag = c.take<int32_t>(sizeof(int32_t));  // zero-filled once by the caller
   e.rec = c.take<float>(H * (G + 2) * e.rec_len * sizeof(float));
   e.blkm = c.take<float>(H * (G + 1) * e.hblocks * sizeof(float));
-  if (e.fused) {
-    e.part_o = c.take<float>(H * e.maxslots * G * D * sizeof(float));
-    e.part_ml = c.take<float>(H * e.maxslots * G * 2 * sizeof(float));
-  }
+  // Partial states are reserved for both shapes, by a bound on H * maxslots that grows with
+  // the rows and with the heads (slots() is at most hblocks + 1, and at most
+  // ceil(2 want / H) + 1 since a workgroup takes at least T / (2 want) blocks): a workspace
+  // sized for long caches or many heads serves the calls with less of either, whichever
+  // shape they take.
+  const size_t parts = std::min({H * (e.hblocks + 1), (size_t)(2 * want) + 2 * H, H * mkv::evict_max_slices()});
+  e.part_o = c.take<float>(parts * G * D * sizeof(float));
+  e.part_ml = c.take<float>(parts * G * 2 * sizeof(float));
   *total = c.off;
   return e;
 }

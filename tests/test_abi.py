@@ -5,6 +5,7 @@ Every call below fails host-side validation (or is a pure size query), so no HIP
 is ever enqueued.
 """
 import ctypes
+import itertools
 import os
 
 import numpy as np
@@ -387,3 +388,22 @@ def test_decode_workspace_is_that_of_the_slices_for_every_shape(heads):
                 assert size[rows, n_split] == decode_bytes_of_slices(p), (heads, d, G, rows)
         for long, short in ((1024, 256), (2048, 256), (1152, 200), (700, 300), (32768, 512)):
             assert size[long, 0] >= size[short, 0], (heads, d, G, long, short)
+
+
+def test_decode_evict_workspace_grows_with_rows_and_heads():
+    """The bytes never grow as the rows or the sequences become fewer, whichever launch shape
+    the calls take, so a workspace sized for the largest call is accepted by every smaller
+    one (48 heads: 336 rows, then 304; 72 heads of 300 rows, then 48)."""
+    batches = (1, 2, 3, 4, 6, 8, 9, 12, 16, 36, 144)
+    rows = (1, 32, 33, 64, 96, 111, 112, 128, 160, 200, 224, 255, 256, 257, 288, 304, 319, 320,
+            336, 352, 512, 1024, 2049, 4096, 32768)
+    for dtype, d, G in itertools.product((0, 1), (64, 128), (1, 4, 16)):
+        size = [[mk.momentkv_decode_evict_workspace_bytes(
+                     dparams(batch=b, n_kv_heads=8, n_q_heads=8 * G, head_dim=d, cap=r, max_len=r,
+                             dtype=dtype)) for r in rows] for b in batches]
+        size = np.array(size)
+        assert (size > 0).all()
+        assert (np.diff(size, axis=0) >= 0).all() and (np.diff(size, axis=1) >= 0).all(), (dtype, d, G)
+    # a fixed number of slices per head likewise
+    size = [mk.momentkv_decode_evict_workspace_bytes(dparams(cap=r, max_len=r, n_split=3)) for r in rows]
+    assert (np.diff(size) >= 0).all()
