@@ -321,7 +321,8 @@ size_t momentkv_decode_evict_workspace_size(const mkv_decode_params* p);  /* sam
  *           max_len >= 320 (256 with at most 64 heads, 112 in fp32; or n_split > 0) one
  *           read of the cache, the attention computed
  *           in the scoring pass over about one workgroup per CU (n_split per KV head when
- *           n_split > 0) and the evicted row's term removed from it afterwards, then a
+ *           n_split > 0) and the evicted row's term removed from it afterwards (computed
+ *           again where the term is more than a quarter of what remains), then a
  *           finishing launch; for shorter caches one launch with one workgroup per KV
  *           head that scores, selects, updates and then attends to the new cache.
  *           Results agree within the dtype's tolerance either way

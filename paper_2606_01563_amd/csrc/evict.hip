@@ -29,8 +29,8 @@
 //   argmin of log2 alpha_j + y_j (the lowest row on ties), the rank-one update n_e += 1,
 //   s_k += k*, s_v += v*, S += v* k*^T (App. A.1 Eq. app_update) and the move of the last
 //   row into the freed slot.  The evicted row's term leaves the attention state; where it
-//   held nearly all of a query's mass (the rest would then keep few significant digits)
-//   the attention over the new cache is computed again instead.  Last, S_tilde q from the
+//   is more than a quarter of what remains (whose rounding would grow with it) the
+//   attention over the new cache is computed again instead.  Last, S_tilde q from the
 //   updated summary and the correction w_R f_R + (1 - w_R) (v_bar + (scale / n_e)
 //   S_tilde q) with the Jensen estimate of the evicted mass (Eqs. fhat, jensen, fused).
 // Short caches: k_evict_attn without the attention, one workgroup per head (two per CU),
@@ -51,8 +51,11 @@ constexpr int kEvTB = 32;           // rows per block
 constexpr int kFinWaves = 4;        // waves of a finishing workgroup
 constexpr int kMaxSlices = 64;      // partial states merged by one finishing wave
 constexpr int kShortRows = 320;     // rows of a head in the short-cache launch, at most
-constexpr float kRedoRatio = 16.f;  // recompute when a removed term exceeds this many
-                                    // times what remains of a query's sum
+// The evicted row's term is taken out of a query's accumulated sums only where it is at most
+// this share of what remains, in the weights and in the output's largest entry: the rounding
+// of the sums then grows by at most as much.  Otherwise (a row that holds a fifth of a query's
+// weight, or a value that dwarfs the rest) the attention is computed again.
+constexpr float kRedoRatio = 0.25f;
 
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
@@ -673,6 +676,13 @@ __device__ __forceinline__ void select_finish(const EvictArgs& e, int head, int 
   // its block's running max mb, scaled to the merged max M (the sum holds p in fp32, the
   // output p rounded to the element type).
   if (ATTN && js >= 0) {
+    float vj[CPL], vmax = 0.f;
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) {
+      vj[c] = sl.kv[1][lane * CPL + c];
+      vmax = fmaxf(vmax, fabsf(vj[c]));
+    }
+    vmax = wave_max(vmax);
 #pragma unroll
     for (int k = 0; k < KQ; ++k) {
       const int g = wave + NW * k;
@@ -682,10 +692,15 @@ __device__ __forceinline__ void select_finish(const EvictArgs& e, int head, int 
           const float s = fast_exp2(mbj[k] - qs.M[k]);
           const float pl = pj * s, po = EA::p_held(pj) * s;
           const float l2 = qs.l[k] - pl;
+          float left = 0.f;  // the lane's largest entry that remains
 #pragma unroll
-          for (int c = 0; c < CPL; ++c) qs.o[k][c] = fmaf(-po, sl.kv[1][lane * CPL + c], qs.o[k][c]);
+          for (int c = 0; c < CPL; ++c) {
+            qs.o[k][c] = fmaf(-po, vj[c], qs.o[k][c]);
+            left = fmaxf(left, fabsf(qs.o[k][c]));
+          }
           qs.l[k] = l2;
-          if (!(kRedoRatio * l2 >= pl) && lane == 0) sl.redo = 1;
+          const bool o_ok = __any(kRedoRatio * left >= po * vmax);
+          if (!(kRedoRatio * l2 >= pl && o_ok) && lane == 0) sl.redo = 1;
         }
       }
     }

@@ -1007,15 +1007,16 @@ def test_evict_group_sizes_and_long_caches(G, budget):
 
 
 @pytest.mark.parametrize("n_split", [1, 3])
-@pytest.mark.parametrize("gap,exact", [(5.0, False), (7.5, False), (12.0, True), (40.0, True)])
+@pytest.mark.parametrize("gap,exact", [(3.0, False), (5.0, False), (7.5, False), (12.0, True),
+                                       (40.0, True)])
 def test_evict_row_that_holds_most_of_the_attention(gap, exact, n_split):
     """The evicted row is one the summary predicts, and its key sits `gap` logits above the
     rest for every query (G = 4, fp32 caches, one workgroup per head or three slices).
     Predicted: v_j = v_bar + scale / n_e S_tilde k_j up to fp32 rounding; or exactly, with
-    a summary of zero values (S_tilde = v_bar = 0) and v_j = 0.  At gap 5 the row holds
-    about half of each query's mass and at 7.5 about 92%: its term leaves the accumulated
-    attention in place.  At 12 (99.9%) and 40 (all but ~1e-17) too little would remain,
-    and the attention over the new cache is computed again."""
+    a summary of zero values (S_tilde = v_bar = 0) and v_j = 0.  At gap 3 the row holds
+    about a tenth of each query's mass: its term leaves the accumulated attention in place.
+    At 5 (about half), 7.5 (92%), 12 (99.9%) and 40 (all but ~1e-17) too little would
+    remain, and the attention over the new cache is computed again."""
     d, G, n, n_ev, js = 128, 4, 100, 50, 37
     rng = np.random.default_rng(11)
     K = rng.standard_normal((n + 1, d))
@@ -1040,6 +1041,45 @@ def test_evict_row_that_holds_most_of_the_attention(gap, exact, n_split):
            "q_dec": f32(Q)[None, None], "k_new": f32(rng.standard_normal(d))[None, None, None],
            "v_new": f32(rng.standard_normal(d))[None, None, None]}
     announce(f"evict dominant row gap={gap} exact={exact} n_split={n_split}")
+    worst, swaps, nev = P.run_evict_steps(inp, comp, 1, n, n_split=n_split)
+    announce(f"worst rel err {worst:.2e}")
+    assert nev == 1 and swaps == 0
+
+
+@pytest.mark.parametrize("n_split", [0, 1, 3])
+def test_evict_row_whose_value_dwarfs_the_rest(n_split):
+    """The evicted row's values are 8192 where the others are about 1, at a tenth of each
+    query's mass, and the summary predicts them exactly (fp32, d = 64, G = 4, 130 rows): left
+    in an accumulated sum, the term's rounding would be 1e-4 of what remains.  Every power
+    of two below makes the row's residual exactly zero: S = M n_e u e_0^T with v_j = scale M
+    k_j[0] u and s_v = 0, all other keys and every query without a component along e_0; the
+    evicted keys' mean lies far from the queries, so the correction has no weight."""
+    d, G, n, n_ev, js, gap = 64, 4, 130, 64, 37, 3.0
+    rng = np.random.default_rng(12)
+    scale = 0.125
+    K, V = rng.standard_normal((n + 1, d)), rng.standard_normal((n + 1, d))
+    u = rng.choice([-1.0, 1.0], d)
+    q0 = rng.standard_normal(d)
+    Q = q0 + 0.1 * rng.standard_normal((G, d))
+    K[:, 0], Q[:, 0], q0[0] = 0.0, 0.0, 0.0
+    K[js] = gap / scale * q0 / (q0 @ q0)
+    K[js, 0] = 8.0
+    V[js] = 8192.0 * u
+    M = 8192.0 / (scale * 8.0)
+    S = M * n_ev * np.outer(u, np.eye(d)[0])
+    s_k = -n_ev * 60.0 / scale * q0 / (q0 @ q0)
+    f32 = lambda a: torch.tensor(np.asarray(a, np.float32)).cuda()
+    comp = types.SimpleNamespace(k_out=f32(K)[None, None], v_out=f32(V)[None, None],
+                                 lens=torch.tensor([[n]], dtype=torch.int32).cuda(),
+                                 n_e=torch.tensor([[n_ev]], dtype=torch.int32).cuda(),
+                                 s_k=f32(s_k)[None, None], s_v=torch.zeros(1, 1, d).cuda(),
+                                 S=f32(S)[None, None])
+    k_new = rng.standard_normal(d)
+    k_new[0] = 0.0
+    inp = {"k": comp.k_out, "q_win": torch.zeros(1, G, 1, d).cuda(),
+           "q_dec": f32(Q)[None, None], "k_new": f32(k_new)[None, None, None],
+           "v_new": f32(rng.standard_normal(d))[None, None, None]}
+    announce(f"evict row of large values n_split={n_split}")
     worst, swaps, nev = P.run_evict_steps(inp, comp, 1, n, n_split=n_split)
     announce(f"worst rel err {worst:.2e}")
     assert nev == 1 and swaps == 0
