@@ -318,9 +318,9 @@ size_t momentkv_decode_evict_workspace_size(const mkv_decode_params* p);  /* sam
 /* p         as for momentkv_decode_attn with summary = 0: S is the raw sum, updated in
  *           place.  max_len bounds lens after the append (budget < max_len <= cap leaves
  *           room for the new row).  n_split selects the launch shape: 0 = automatic; for
- *           max_len >= 320 (256 with at most 64 heads, 112 in fp32; or n_split > 0) one
- *           read of the cache, the attention computed
- *           in the scoring pass over about one workgroup per CU (n_split per KV head when
+ *           max_len >= 320 (from 256 with few heads, from 112 in fp32, by type, head_dim,
+ *           queries per head and heads; or n_split > 0) one read of the cache, the attention
+ *           computed in the scoring pass over about one workgroup per CU (n_split per KV head when
  *           n_split > 0) and the evicted row's term removed from it afterwards (computed
  *           again where the term is more than a quarter of what remains), then a
  *           finishing launch; for shorter caches one launch with one workgroup per KV

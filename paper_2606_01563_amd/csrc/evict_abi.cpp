@@ -29,24 +29,53 @@ namespace {
 // Workspace: the flag first, then the score records and the per-block running maxima, then
 // the heads' partial states (fused).
 constexpr int kCUs = 256;
-// max_len from which the one-read shape runs.  Measured per call (d = 128, G = 4), short
-// against one-read shape, us:
-//   bf16   8 heads    200 rows 21.8 / 20.4   300 rows 25.7 / 20.6
-//          32 heads   200 rows 22.0 / 23.7   300 rows 26.0 / 23.9
-//          64 heads   200 rows 22.4 / 25.4   300 rows 26.4 / 25.4
-//          288 heads  200 rows 33.1 / 38.9   300 rows 41.2 / 42.6
-//   fp32   8 heads     64 rows 31.1 / 29.0   128 rows 46.8 / 29.2
-//          64 heads    64 rows 31.8 / 34.1   128 rows 49.4 / 34.8
-//          288 heads   64 rows 52.8 / 59.3   128 rows 75.1 / 72.1   300 rows 124 / 87
-// (few heads leave CUs idle that the one-read shape shares out; in fp32 a block's products
-// take the one workgroup of a head several times as long, and it has the registers for few
-// waves).
-constexpr int kFusedMinLen = 320, kFusedMinLenFew = 256, kFusedMinLenF32 = 112;
-constexpr int kFewHeads = 64;
+// max_len from which the one-read shape runs.  Measured per call, every head evicting, short
+// against one-read shape, us (swept over 17 numbers of heads, 12 lengths and 1 to 16 queries
+// per KV head; more than 320 rows do not fit the short launch's records):
+//   bf16 d 128, G 4     8 heads 256 rows 23.1 / 20.5    32 heads 256 rows 23.3 / 24.2
+//                      32 heads 288 rows 25.9 / 24.3    48 heads 288 rows 26.2 / 31.2
+//                      64 heads 288 rows 26.3 / 26.1
+//   bf16 d 128, G 16   32 heads 288 rows 38.6 / 38.7    d 64, G 4  8 heads 256 rows 13.3 / 14.9
+//   fp32 d 128, G 4     8 heads 112 rows 37.2 / 29.1    64 heads 112 rows 37.9 / 33.9
+//                      96 heads 128 rows 41.6 / 50.3    96 heads 160 rows 54.1 / 50.2
+//                     128 heads 112 rows 42.5 / 36.8   192 heads 128 rows 45.2 / 52.1
+//                     192 heads 160 rows 57.6 / 56.5   256 heads 112 rows 47.5 / 35.0
+//                     288 heads 160 rows 77.7 / 72.7   400 heads 192 rows 89.2 / 91.6
+//   fp32 d 128, G 8    32 heads 112 rows 36.4 / 36.1    96 heads 128 rows 37.5 / 56.7
+//                      48 heads 256 rows 52.0 / 55.0    64 heads 160 rows 46.5 / 40.2
+//   fp32 d 128, G 16    8 heads 112 rows 43.4 / 43.7    32 heads 160 rows 53.8 / 46.1
+//   fp32 d 64, G 4     64 heads 112 rows 19.0 / 18.1    96 heads 160 rows 23.7 / 24.7
+//                     192 heads 192 rows 25.5 / 27.5   256 heads 112 rows 19.7 / 18.5
+//                     400 heads 224 rows 40.3 / 41.4
+//   fp32 d 64, G 8    128 heads 112 rows 21.9 / 21.8   160 heads 224 rows 30.4 / 34.0
+//                     256 heads 160 rows 27.2 / 28.4   400 heads 319 rows 58.3 / 63.2
+//   fp32 d 64, G 16     8 heads 128 rows 26.0 / 26.5     8 heads 160 rows 30.9 / 26.6
+// Few heads leave CUs idle that the one-read shape shares out, and in fp32 a block's products
+// take the one workgroup of a head several times as long.  Above 64 heads the shares of the
+// workgroups cross heads (a second setup and partial state) unless the heads divide the CUs.
+// The lines are drawn where no evicting call is slower than with the short launch.  (Where no
+// head evicts, the second launch makes the call longer: bf16, 8 heads 288 rows 14.1 / 15.3.)
+constexpr int kFusedMinLen = 320;
 
 int fused_min_len(const mkv_decode_params* p) {
-  if (p->dtype == MKV_F32) return kFusedMinLenF32;
-  return (int64_t)p->batch * p->n_kv_heads <= kFewHeads ? kFusedMinLenFew : kFusedMinLen;
+  const int64_t heads = (int64_t)p->batch * p->n_kv_heads;
+  const int G = p->n_q_heads / p->n_kv_heads;
+  const bool d64 = p->head_dim == 64;
+  if (p->dtype != MKV_F32) {
+    if (d64 || G > 8 || heads > 32) return kFusedMinLen;
+    return heads <= 16 ? 256 : 257;
+  }
+  if (!d64 && G > 4) {
+    if (heads <= 32) return G <= 8 ? 112 : 160;
+    return heads == 64 ? 160 : kFusedMinLen;
+  }
+  if (heads <= 64 || kCUs % heads == 0) {  // G > 4 here and below: d = 64
+    if (G <= 8) return G <= 4 || heads <= 128 ? 112 : 192;
+    return heads <= 64 ? 160 : kFusedMinLen;
+  }
+  if (!d64) return heads <= 288 ? 160 : 224;
+  if (G <= 4) return heads <= 288 ? 224 : 256;
+  return G <= 8 && heads <= 288 ? 256 : kFusedMinLen;
 }
 
 mkv::EvictArgs evict_layout(const mkv_decode_params* p, int32_t budget, void* ws, size_t* total) {

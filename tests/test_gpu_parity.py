@@ -913,19 +913,70 @@ def test_evict_budgets_and_lengths_around_the_bound(dtype, d, n_split):
     P.run_evict_steps(gpu, out, 2, 289, flag=8, n_split=n_split)         # above budget
 
 
+def evict_shape(dtype, d, G, heads, rows):
+    """The automatic launch shape of an eviction call, from whether it writes partial states
+    (past the records and block maxima of its workspace): "one read" or "short"."""
+    q, kc, vc, lens, n_e, s_k, s_v, S = _decode_state(1, G, d, rows, 1, batch=heads, dtype=dtype)
+    lens.fill_(rows - 1)
+    new = torch.randn(heads, 1, d, device="cuda").to(dtype)
+    p = mk.decode_params(q, kc, max_len=rows)
+    ws = torch.full((mk.momentkv_decode_evict_workspace_bytes(p),), 0xFF, dtype=torch.uint8, device="cuda")
+    ws[:256] = 0
+    res = mk.momentkv_decode_evict(q, kc, vc, lens, n_e, s_k, s_v, S, new, new, rows - 1, workspace=ws)
+    assert res[4] is ws and int(lens.min()) == int(lens.max()) == rows - 1
+    blocks, up = -(-rows // 32), lambda x: -(-x // 256) * 256
+    parts = 256 + up(heads * (G + 2) * 32 * blocks * 4) + up(heads * (G + 1) * blocks * 4)
+    return "one read" if bool((ws[parts:] != 0xFF).any()) else "short"
+
+
+EVICT_LINES = {  # (dtype, d, G): [(heads, first rows of the one-read shape)]
+    ("bf16", 128, 4): [(1, 256), (16, 256), (17, 257), (32, 257), (33, 320), (288, 320)],
+    ("bf16", 128, 8): [(8, 256)], ("bf16", 128, 16): [(8, 320)], ("bf16", 64, 4): [(8, 320)],
+    ("fp32", 128, 4): [(8, 112), (64, 112), (65, 160), (128, 112), (256, 112), (288, 160), (289, 224)],
+    ("fp32", 128, 8): [(32, 112), (33, 320), (64, 160), (65, 320)],
+    ("fp32", 128, 16): [(32, 160), (64, 160), (128, 320)],
+    ("fp32", 64, 4): [(64, 112), (65, 224), (128, 112), (288, 224), (289, 256)],
+    ("fp32", 64, 8): [(128, 112), (256, 192), (96, 256), (289, 320)],
+    ("fp32", 64, 16): [(64, 160), (65, 320)],
+}
+
+
+@pytest.mark.parametrize("key", list(EVICT_LINES), ids=lambda k: "-".join(map(str, k)))
+def test_evict_launch_shape_lines(key):
+    """The automatic launch shape on both sides of its lines in rows and heads."""
+    dtype, d, G = key
+    for heads, rows in EVICT_LINES[key]:
+        announce(f"evict {key} heads {heads} rows {rows}")
+        dt = torch.float32 if dtype == "fp32" else torch.bfloat16
+        assert evict_shape(dt, d, G, heads, rows - 1) == "short", (heads, rows)
+        assert evict_shape(dt, d, G, heads, rows) == "one read", (heads, rows)
+
+
+@pytest.mark.parametrize("d,G,budget", [(128, 8, 110), (128, 8, 111), (128, 16, 158), (128, 16, 159),
+                                        (64, 16, 158), (64, 16, 159)])
+def test_evict_fp32_wide_groups_at_the_launch_shape_bound(d, G, budget):
+    """Both sides of the row bounds of fp32 groups of 8 and 16 queries (max_len 112 and 160)."""
+    wl, cpu, gpu = layer("tiny_fp32_n2048", steps=3, dtype=torch.float32, head_dim=d, ctx_len=600,
+                         batch=1, n_q_heads=2 * G, n_kv_heads=2, window=16, budgets=(budget,))
+    out = P.run_compress(gpu, budget, cap=budget + 1)
+    announce(f"evict fp32 d={d} G={G} budget={budget}")
+    worst, swaps, n = P.run_evict_steps(gpu, out, 3, budget)
+    assert n == 3 * 2
+
+
 @pytest.mark.parametrize("budget", [318, 319])
 def test_evict_at_the_launch_shape_bound(budget):
     """Caches of 319 and 320 rows (max_len = budget + 1), the two sides of the automatic
-    choice between the short-cache launch and the one-read shape (G = 4, bf16, d = 128):
-    both follow the oracle's trajectory."""
+    choice between the short-cache launch and the one-read shape for more than 32 heads
+    (G = 4, bf16, d = 128): both follow the oracle's trajectory."""
     wl, cpu, gpu = layer("tiny_fp32_n2048", steps=3, dtype=torch.bfloat16, head_dim=128,
-                         ctx_len=1200, batch=1, n_q_heads=8, n_kv_heads=2, window=16,
+                         ctx_len=1200, batch=17, n_q_heads=8, n_kv_heads=2, window=16,
                          budgets=(budget,))
     out = P.run_compress(gpu, budget, cap=budget + 1)
     announce(f"evict at the shape bound: budget {budget}, max_len {budget + 1}")
     worst, swaps, n = P.run_evict_steps(gpu, out, 3, budget)
     announce(f"worst rel err {worst:.2e}, swaps {swaps} of {n}")
-    assert n == 3 * 2
+    assert n == 3 * 34
 
 
 @pytest.mark.parametrize("dtype,budget", [(torch.bfloat16, 254), (torch.bfloat16, 255),
@@ -941,11 +992,12 @@ def test_evict_at_the_bounds_for_few_heads_and_fp32(dtype, budget):
     announce(f"{dtype} budget {budget}: worst {worst:.2e}, near-tie swaps {swaps}")
 
 
-@pytest.mark.parametrize("n_split,ctx", [(0, 300), (0, 700), (1, 700)])
+@pytest.mark.parametrize("n_split,ctx", [(0, 200), (0, 300), (0, 700), (1, 700)])
 def test_evict_with_empty_summary_scores_alpha_times_value_norm(n_split, ctx):
     """Budget above the context keeps every token, so n_e = 0: the first evictions use
     v_bar = S_tilde = 0 and later ones the summary they build (the short-cache launch at
-    300 rows, the one-read shape at 700 rows over all CUs and one workgroup per head)."""
+    200 rows, the one-read shape at 300 and 700 rows over all CUs and at 700 with one
+    workgroup per head)."""
     wl, cpu, gpu = layer("tiny_fp32_n2048", steps=6, dtype=torch.bfloat16, head_dim=128,
                          ctx_len=ctx, batch=1, n_q_heads=4, n_kv_heads=2, window=16,
                          budgets=(900,))
