@@ -86,8 +86,12 @@ mkv::CompressArgs compress_layout(const mkv_compress_params* p, void* ws, size_t
   a.nsl1 = ceil_div(a.ntile, a.tps1);
   // window-mass pass: about 512 workgroups of 256 threads, two per CU, so that all of them
   // run at once (each start costs the queries and the first keys: about 4 us; 128K context,
-  // 1024 workgroups 100 us, 512 workgroups 89)
-  a.nsl2 = clampi(ceil_div(512, a.H), 1, a.ntile);
+  // 1024 workgroups 100 us, 512 workgroups 89).  fp32 with more than 32 heads that do not
+  // divide 512: about 1024, since a few workgroups more than 512 are a second round of long
+  // ones (a call of d 64, 512 window rows, 80 heads of 6000 tokens: 1043 us against 1125 with
+  // 560 workgroups; up to 32 heads 512 are up to 9% of a call faster).
+  const bool many = p->dtype == MKV_F32 && a.H > 32 && 512 % a.H != 0;
+  a.nsl2 = clampi(ceil_div(many ? 1024 : 512, a.H), 1, a.ntile);
   a.tps2 = std::min(ceil_div(a.ntile, a.nsl2), mkv::kMassMaxTiles);
   a.nsl2 = ceil_div(a.ntile, a.tps2);
   // top-k slices of 2048 candidates (at most 512 for kMaxCandidates); each slice's

@@ -469,6 +469,17 @@ def test_several_moment_rounds(dtype, mi_rounds, budget):
         assert not torch.equal(one.score, out.score)
 
 
+@pytest.mark.parametrize("heads", [32, 36])
+def test_fp32_compress_on_both_sides_of_the_window_mass_split(heads):
+    """fp32 layers of 32 heads (16 window-mass slices per head) and 36 (29): three heads
+    against the oracle."""
+    wl, cpu, gpu = layer("tiny_fp32_n2048", ctx_len=3000, batch=heads // 4, n_q_heads=8, n_kv_heads=4,
+                         head_dim=64, window=16, budgets=(200,))
+    out = P.run_compress(gpu, 200, cap=200)
+    for b, h in ((0, 0), (heads // 8, 1), (heads // 4 - 1, 3)):
+        announce(f"heads {heads}: {P.check_compress_head(cpu, out, b, h, 200)}")
+
+
 def test_budget_equal_to_protected_tokens_evicts_every_candidate():
     wl, cpu, gpu = layer("tiny_fp32_n2048", steps=2, ctx_len=300)
     L = 1 + wl.window
