@@ -423,6 +423,7 @@ struct SelLds {
   float kv[2][D];      // k*, v* of the evicted row
   float sk[D], sv[D];  // s_k, s_v after this call
   float sq[GM * D];    // S_tilde q (unscaled), query-major
+  float vm[2];         // largest |v*| of each half (one-read shape)
 };
 
 // S after the update, staged in LDS for S_tilde q: element (row, col) in 16-byte chunks
@@ -647,6 +648,10 @@ __device__ __forceinline__ void select_finish(const EvictArgs& e, int head, int 
       svv += vf;
       e.s_k[(size_t)head * D + tid] = skv;
       e.s_v[(size_t)head * D + tid] = svv;
+      if constexpr (ATTN) {  // (while the stores complete, which the barrier waits for)
+        const float vm = wave_max(fabsf(vf));
+        if (lane == 0) sl.vm[wave] = vm;
+      }
     }
     if (tid == 0) {
       e.n_e[head] = ne + 1;
@@ -676,13 +681,8 @@ __device__ __forceinline__ void select_finish(const EvictArgs& e, int head, int 
   // its block's running max mb, scaled to the merged max M (the sum holds p in fp32, the
   // output p rounded to the element type).
   if (ATTN && js >= 0) {
-    float vj[CPL], vmax = 0.f;
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) {
-      vj[c] = sl.kv[1][lane * CPL + c];
-      vmax = fmaxf(vmax, fabsf(vj[c]));
-    }
-    vmax = wave_max(vmax);
+    float vmax = sl.vm[0];  // the row's largest value
+    if constexpr (D > kWave) vmax = fmaxf(vmax, sl.vm[1]);
 #pragma unroll
     for (int k = 0; k < KQ; ++k) {
       const int g = wave + NW * k;
@@ -695,7 +695,7 @@ __device__ __forceinline__ void select_finish(const EvictArgs& e, int head, int 
           float left = 0.f;  // the lane's largest entry that remains
 #pragma unroll
           for (int c = 0; c < CPL; ++c) {
-            qs.o[k][c] = fmaf(-po, vj[c], qs.o[k][c]);
+            qs.o[k][c] = fmaf(-po, sl.kv[1][lane * CPL + c], qs.o[k][c]);
             left = fmaxf(left, fabsf(qs.o[k][c]));
           }
           qs.l[k] = l2;
