@@ -17,7 +17,7 @@ using namespace mkv::abi;
 namespace {
 
 // ------------------------------------------------------------------ decode + eviction
-// Two launch shapes.  Fused (one read of the cache; from fused_min_len() rows, or whenever
+// Two launch shapes.  Fused (one read of the cache; where one_read() says, or whenever
 // n_split > 0): the scoring launch has one workgroup per CU of the target (kCUs; n_split
 // per head when n_split > 0), each taking an equal contiguous share of the flattened
 // (head, 32-row block) range, so that a head has at most maxslots partial states (at most
@@ -29,9 +29,9 @@ namespace {
 // Workspace: the flag first, then the score records and the per-block running maxima, then
 // the heads' partial states (fused).
 constexpr int kCUs = 256;
-// max_len from which the one-read shape runs.  Measured per call, every head evicting, short
-// against one-read shape, us (swept over 17 numbers of heads, 12 lengths and 1 to 16 queries
-// per KV head; more than 320 rows do not fit the short launch's records):
+// Where the one-read shape runs.  Measured per call, every head evicting, short against
+// one-read shape, us (fp32 swept over 33 numbers of heads, bf16 over 17, 8 to 12 lengths and
+// 1 to 16 queries per KV head; 320 rows and more do not fit the short launch's records):
 //   bf16 d 128, G 4     8 heads 256 rows 23.1 / 20.5    32 heads 256 rows 23.3 / 24.2
 //                      32 heads 288 rows 25.9 / 24.3    48 heads 288 rows 26.2 / 31.2
 //                      64 heads 288 rows 26.3 / 26.1
@@ -40,42 +40,55 @@ constexpr int kCUs = 256;
 //                      96 heads 128 rows 41.6 / 50.3    96 heads 160 rows 54.1 / 50.2
 //                     128 heads 112 rows 42.5 / 36.8   192 heads 128 rows 45.2 / 52.1
 //                     192 heads 160 rows 57.6 / 56.5   256 heads 112 rows 47.5 / 35.0
-//                     288 heads 160 rows 77.7 / 72.7   400 heads 192 rows 89.2 / 91.6
+//                     288 heads 128 rows 65.1 / 62.3   400 heads 192 rows 89.2 / 91.6
 //   fp32 d 128, G 8    32 heads 112 rows 36.4 / 36.1    96 heads 128 rows 37.5 / 56.7
-//                      48 heads 256 rows 52.0 / 55.0    64 heads 160 rows 46.5 / 40.2
+//                      48 heads 160 rows 46.4 / 37.5    48 heads 256 rows 52.0 / 55.0
 //   fp32 d 128, G 16    8 heads 112 rows 43.4 / 43.7    32 heads 160 rows 53.8 / 46.1
 //   fp32 d 64, G 4     64 heads 112 rows 19.0 / 18.1    96 heads 160 rows 23.7 / 24.7
-//                     192 heads 192 rows 25.5 / 27.5   256 heads 112 rows 19.7 / 18.5
-//                     400 heads 224 rows 40.3 / 41.4
+//                     192 heads 192 rows 25.5 / 27.5   288 heads 224 rows 38.4 / 33.5
 //   fp32 d 64, G 8    128 heads 112 rows 21.9 / 21.8   160 heads 224 rows 30.4 / 34.0
-//                     256 heads 160 rows 27.2 / 28.4   400 heads 319 rows 58.3 / 63.2
 //   fp32 d 64, G 16     8 heads 128 rows 26.0 / 26.5     8 heads 160 rows 30.9 / 26.6
 // Few heads leave CUs idle that the one-read shape shares out, and in fp32 a block's products
-// take the one workgroup of a head several times as long.  Above 64 heads the shares of the
-// workgroups cross heads (a second setup and partial state) unless the heads divide the CUs.
-// The lines are drawn where no evicting call is slower than with the short launch.  (Where no
-// head evicts, the second launch makes the call longer: bf16, 8 heads 288 rows 14.1 / 15.3.)
-constexpr int kFusedMinLen = 320;
+// take the one workgroup of a head several times as long.  Once a workgroup's share is more
+// than a block it crosses heads (a second setup and partial state) unless the heads divide the
+// CUs; above 256 heads the short launch runs in two rounds.  The lines are drawn where no
+// evicting call is more than 3% slower than with the short launch.  (Where no head evicts, the
+// second launch makes the call longer: bf16, 8 heads 288 rows 14.1 / 15.3.)
+constexpr int kFusedMinLen = 320, kFusedMinLenF32 = 112;
 
-int fused_min_len(const mkv_decode_params* p) {
+bool one_read(const mkv_decode_params* p) {
+  if (p->n_split > 0 || p->max_len >= kFusedMinLen) return true;
   const int64_t heads = (int64_t)p->batch * p->n_kv_heads;
-  const int G = p->n_q_heads / p->n_kv_heads;
-  const bool d64 = p->head_dim == 64;
-  if (p->dtype != MKV_F32) {
-    if (d64 || G > 8 || heads > 32) return kFusedMinLen;
-    return heads <= 16 ? 256 : 257;
-  }
-  if (!d64 && G > 4) {
-    if (heads <= 32) return G <= 8 ? 112 : 160;
-    return heads == 64 ? 160 : kFusedMinLen;
-  }
-  if (heads <= 64 || kCUs % heads == 0) {  // G > 4 here and below: d = 64
-    if (G <= 8) return G <= 4 || heads <= 128 ? 112 : 192;
-    return heads <= 64 ? 160 : kFusedMinLen;
-  }
-  if (!d64) return heads <= 288 ? 160 : 224;
-  if (G <= 4) return heads <= 288 ? 224 : 256;
-  return G <= 8 && heads <= 288 ? 256 : kFusedMinLen;
+  const int G = p->n_q_heads / p->n_kv_heads, wide = G <= 4 ? 0 : G <= 8 ? 1 : 2;
+  if (p->dtype != MKV_F32)
+    return p->head_dim == 128 && G <= 8 && heads <= 32 && p->max_len >= (heads <= 16 ? 256 : 257);
+  if (p->max_len < kFusedMinLenF32) return false;
+  // fp32: the least number of 32-row blocks, by heads (rows) and d = 64, 128 with up to 4, 8
+  // and 16 queries per head; 11 blocks are never short
+  static constexpr int kBlocks[9][2][3] = {
+      {{4, 4, 5}, {4, 4, 5}},      // up to 32 heads, or a block per workgroup at most
+      {{5, 6, 8}, {5, 9, 9}},      // up to 63
+      {{5, 5, 5}, {5, 5, 5}},      // 64
+      {{6, 7, 9}, {5, 10, 10}},    // up to 127
+      {{4, 4, 6}, {4, 7, 7}},      // 128
+      {{7, 8, 10}, {5, 11, 11}},   // up to 255
+      {{4, 6, 8}, {4, 11, 11}},    // 256
+      {{6, 10, 10}, {4, 10, 10}},  // up to 320
+      {{8, 11, 11}, {7, 11, 11}},  // more
+  };
+  const int blocks = ceil_div(p->max_len, 32);
+  const int row = heads <= 32 || heads * blocks <= kCUs ? 0
+                  : heads < 64                          ? 1
+                  : heads == 64                         ? 2
+                  : heads < 128                         ? 3
+                  : heads == 128                        ? 4
+                  : heads < 256                         ? 5
+                  : heads == 256                        ? 6
+                  : heads <= 320                        ? 7
+                                                        : 8;
+  const bool d128 = p->head_dim == 128;
+  if (row == 0 && d128 && wide == 1 && heads > 32) return blocks >= 5;
+  return blocks >= kBlocks[row][d128][wide];
 }
 
 mkv::EvictArgs evict_layout(const mkv_decode_params* p, int32_t budget, void* ws, size_t* total) {
@@ -91,7 +104,7 @@ mkv::EvictArgs evict_layout(const mkv_decode_params* p, int32_t budget, void* ws
   e.tau = p->tau;
   e.hblocks = ceil_div(p->max_len, 32);
   e.rec_len = 32 * e.hblocks;
-  e.fused = (p->n_split > 0 || p->max_len >= fused_min_len(p)) ? 1 : 0;
+  e.fused = one_read(p) ? 1 : 0;
   const size_t H = e.n_heads, G = e.G, D = p->head_dim;
   Carver c;
   c.base = static_cast<char*>(ws);

@@ -943,12 +943,14 @@ def evict_shape(dtype, d, G, heads, rows):
 EVICT_LINES = {  # (dtype, d, G): [(heads, first rows of the one-read shape)]
     ("bf16", 128, 4): [(1, 256), (16, 256), (17, 257), (32, 257), (33, 320), (288, 320)],
     ("bf16", 128, 8): [(8, 256)], ("bf16", 128, 16): [(8, 320)], ("bf16", 64, 4): [(8, 320)],
-    ("fp32", 128, 4): [(8, 112), (64, 112), (65, 160), (128, 112), (256, 112), (288, 160), (289, 224)],
-    ("fp32", 128, 8): [(32, 112), (33, 320), (64, 160), (65, 320)],
-    ("fp32", 128, 16): [(32, 160), (64, 160), (128, 320)],
-    ("fp32", 64, 4): [(64, 112), (65, 224), (128, 112), (288, 224), (289, 256)],
-    ("fp32", 64, 8): [(128, 112), (256, 192), (96, 256), (289, 320)],
-    ("fp32", 64, 16): [(64, 160), (65, 320)],
+    ("fp32", 128, 4): [(8, 112), (64, 112), (72, 129), (128, 112), (192, 129), (256, 112),
+                       (288, 112), (320, 112), (321, 193)],
+    ("fp32", 128, 8): [(32, 112), (48, 129), (63, 257), (64, 129), (72, 289), (128, 193), (192, 320),
+                       (256, 320), (257, 289), (321, 320)],
+    ("fp32", 128, 16): [(32, 129), (51, 129), (64, 129), (127, 289), (128, 193), (129, 320)],
+    ("fp32", 64, 4): [(64, 112), (65, 161), (128, 112), (129, 193), (256, 112), (320, 161), (321, 225)],
+    ("fp32", 64, 8): [(64, 112), (63, 161), (65, 193), (128, 112), (129, 225), (256, 161), (257, 289)],
+    ("fp32", 64, 16): [(51, 129), (63, 225), (64, 129), (65, 257), (128, 161), (129, 289), (256, 225)],
 }
 
 
@@ -963,10 +965,10 @@ def test_evict_launch_shape_lines(key):
         assert evict_shape(dt, d, G, heads, rows) == "one read", (heads, rows)
 
 
-@pytest.mark.parametrize("d,G,budget", [(128, 8, 110), (128, 8, 111), (128, 16, 158), (128, 16, 159),
-                                        (64, 16, 158), (64, 16, 159)])
+@pytest.mark.parametrize("d,G,budget", [(128, 8, 110), (128, 8, 111), (128, 16, 127), (128, 16, 128),
+                                        (64, 16, 127), (64, 16, 128)])
 def test_evict_fp32_wide_groups_at_the_launch_shape_bound(d, G, budget):
-    """Both sides of the row bounds of fp32 groups of 8 and 16 queries (max_len 112 and 160)."""
+    """Both sides of the row bounds of fp32 groups of 8 and 16 queries (max_len 112 and 129)."""
     wl, cpu, gpu = layer("tiny_fp32_n2048", steps=3, dtype=torch.float32, head_dim=d, ctx_len=600,
                          batch=1, n_q_heads=2 * G, n_kv_heads=2, window=16, budgets=(budget,))
     out = P.run_compress(gpu, budget, cap=budget + 1)
