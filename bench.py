@@ -467,7 +467,8 @@ def evict_measurement(args, wl, budgets, stacks, q_steps, kn_steps, vn_steps, ou
                       for L in budgets) / len(budgets)
     return {"what": "per token and budget one momentkv_decode_evict call over the 36 "
                     "caches: append, Phase 1 eviction, Phase 2 corrected attention; cache "
-                    "kept at the budget.  Caches under 320 rows: one k_evict_attn launch that "
+                    "kept at the budget.  Short caches (bf16, more than 32 heads: under 320 "
+                    "rows): one k_evict_attn launch that "
                     "scores, selects, updates and attends to the new cache; above: "
                     "k_evict_attn scoring and attention in one read of the cache, then "
                     "k_evict_finish",
@@ -553,7 +554,7 @@ def main() -> int:
     world = int(os.environ.get("WORLD_SIZE", "1"))
     if args.gpus != 1 or world != 1:
         print("bench.py measures one GPU: the MomentKV hot path shards over (sequence, KV head) "
-              "with no exchange, and this build runs on a single MI355X; use --gpus 1.",
+              "with no exchange, and the library runs on a single MI355X; use --gpus 1.",
               file=sys.stderr)
         return 2
     if not torch.cuda.is_available():
@@ -900,9 +901,9 @@ def main() -> int:
         "compress_ms_per_layer": {k: v["compress_ms_per_layer"] for k, v in per_budget.items()},
         "per_budget": per_budget,
         "roofline": {"kernel": "momentkv_decode_attn call over the stack: one launch, "
-                               "k_decode_fused, k_decode_group or k_decode_slice (the last "
-                               "wave of each head merges it); time per call from the graph "
-                               "replays",
+                               "k_decode_fused (a workgroup per head), k_decode_group or "
+                               "k_decode_slice (the head's last workgroup to arrive merges "
+                               "it); time per call from the graph replays",
                      "bound": "hbm", "achieved": avg_bytes / avg_launch_s / 1e9,
                      "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": avg_bytes / avg_launch_s / 1e9 / HBM_PEAK_GBS,

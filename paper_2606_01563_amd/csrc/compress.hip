@@ -11,22 +11,23 @@
 //   2 k_row_combine   per head: merge the row partials in slice order -> (max, 1/Z);
 //                     add up the slices' slots into slot 0 (the candidates' sums);
 //                     zero the head's two top-k key histograms.
-//   3 k_mass          per (slice, head): logits again, softmax mass summed over the
-//                     window rows -> a_j, aligned chunk pooling -> abar_j,
-//                     provisional score abar_j ||v_j||, added to the key histogram of
-//                     the first selection.                                 [reads K]
-//   4 k_tk_*          per head: radix select of the k_keep best scores, lower position
-//                     first on ties; writes the kept positions in ascending order; each
-//                     slice's workgroup
-//                     then adds the covariance and sums of its kept rows (read through
-//                     their positions), stored negated as a partial slot, or, when the
-//                     head's evicted rows are fewer than its kept ones, of its evicted
-//                     rows, stored as they are.
+//   3 k_mass_stream   (bf16; k_mass in fp32) per (slice, head): logits again, softmax
+//                     mass summed over the window rows -> a_j, aligned chunk pooling ->
+//                     abar_j, provisional score abar_j ||v_j||, added to the key
+//                     histogram of the first selection.                    [reads K]
+//   4 k_tk_*          per head: the k_keep best scores, lower position first on ties, from
+//                     the histogram's bin of the k-th key, which the head's last slice to
+//                     arrive refines; writes the kept positions in ascending order; each
+//                     slice's workgroup then adds the covariance and sums of its kept
+//                     rows (read through their positions), stored negated as a partial
+//                     slot, or, when the head's evicted rows are fewer than its kept
+//                     ones, of its evicted rows, stored as they are.
 //   7 k_reduce        fixed-order sum of the slots = raw moments of the provisional
 //                     evicted set: slot 0 and the kept rows' slots (the candidates' sums
-//                     minus the kept rows'), or only the evicted rows' slots.  Summing the evicted rows directly
-//                     when they are the fewer keeps the cancellation of S_C - S_kept from
-//                     growing with the ratio of candidates to evicted rows.
+//                     minus the kept rows'), or only the evicted rows' slots.  Summing the
+//                     evicted rows directly when they are the fewer keeps the cancellation
+//                     of S_C - S_kept from growing with the ratio of candidates to evicted
+//                     rows.
 //   8 k_residual      per (slice, head): centring and clamp of the provisional summary
 //                     into LDS (fp32, or a bf16 hi/lo pair), S_tilde k_j on MFMA,
 //                     ||v_j - v_bar - c S_tilde k_j||, score_j = abar_j * that norm,

@@ -69,13 +69,7 @@ __device__ __forceinline__ void wave_lds_order() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// ---------------------------------------------------------------- in-launch hand-off
-// Partial results that one workgroup hands to another within the split launch go through
-// agent-scope relaxed atomic stores and loads, which are not served from the per-XCD
-// caches (those are not kept coherent with each other).  A writer waits until its own
-// stores have completed before it counts itself in on the head's arrival counter, and the
-// last arrival reads the partials only after the count, so no device-scope fence is
-// needed (on this part such a fence writes back and invalidates a whole L2).
+// Agent-scope stores and loads of the in-launch hand-off (mkv_device.h), in fp32.
 __device__ __forceinline__ void st_agent(float* p, float v) {
   __hip_atomic_store(reinterpret_cast<uint32_t*>(p), __float_as_uint(v), __ATOMIC_RELAXED,
                      __HIP_MEMORY_SCOPE_AGENT);
@@ -92,6 +86,7 @@ __device__ __forceinline__ float2 ld_agent2(const float* p) {
                                        __HIP_MEMORY_SCOPE_AGENT);
   return make_float2(__uint_as_float((uint32_t)u), __uint_as_float((uint32_t)(u >> 32)));
 }
+
 // Query fragments of one KV head's group (A operand of Q.K^T, B operand of S_tilde q):
 // lane l holds 8 dims at 32 ks + 8 (l / 16) of query query_of(l % 16); queries past G are
 // zero.
@@ -916,8 +911,9 @@ k_decode_slice(DecodeArgs a) {
 // Few heads: one launch of NW-wave workgroups, per head one for S_tilde q and nsplit token
 // groups of split_len rows.  A group's waves take its 32-row blocks w, w + NW, ... (a block
 // is about 1.5 us of dependent work for its wave, so more waves rather than more blocks in
-// flight: a second register set measured slower) and merge their states in LDS, so a head has at most kMaxGroups partials, which the last workgroup
-// of the head to arrive reads in one round trip (one query per wave).
+// flight: a second register set measured slower) and merge their states in LDS, so a head has
+// at most kMaxGroups partials, which the last workgroup of the head to arrive reads in one
+// round trip (one query per wave).
 template <class T, int D, int GMAX, int PREP, int NW>
 __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_decode_group(DecodeArgs a) {
   typedef BlockAttn<T, D, GMAX> BA;

@@ -222,9 +222,11 @@ __device__ __forceinline__ int query_of(int row) { return 4 * (row & 3) + (row >
 
 // ---------------------------------------------------------------- in-launch hand-off
 // Results that one workgroup hands to another of the same launch go through agent-scope
-// relaxed atomic stores and loads, which are not served from the per-XCD caches.  A writer
-// waits until its own stores have completed (stores_complete) before it counts itself in,
-// and the last to arrive reads only after the count (loads_after_count).
+// relaxed atomic stores and loads, which are not served from the per-XCD caches (those are
+// not kept coherent with each other).  A writer waits until its own stores have completed
+// (stores_complete) before it counts itself in, and the last to arrive reads only after the
+// count (loads_after_count), so no device-scope fence is needed (on this part such a fence
+// writes back and invalidates a whole L2).
 // s_waitcnt with vmcnt = 0 and the other counters at their maximum: every vector memory
 // operation of the wave issued so far (stores included) has completed.
 constexpr int kWaitVmem = 0x0F70;
