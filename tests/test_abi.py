@@ -342,8 +342,10 @@ def test_decode_plan_of_equal_values_of_other_types_is_refused():
     refused after a call with the equal integer."""
     ok = (1, 4, 1, 64, 128, 128, 1, 1, 0.0, 1e-6, 0, 0)
     assert mk._decode_plan(*ok)[1] > 0
-    with pytest.raises(TypeError):
-        mk._decode_plan(*ok[:5], 128.0, *ok[6:])
+    for i in (5, 6, 10, 11):  # max_len, order, n_split, summary
+        with pytest.raises(TypeError):
+            mk._decode_plan(*ok[:i], float(ok[i]), *ok[i + 1:])
+    assert mk._decode_plan(*ok[:8], 0, *ok[9:])[1] == mk._decode_plan(*ok)[1]
 
 
 @pytest.mark.parametrize("make", [torch.tensor, np.array], ids=["tensor", "array"])
