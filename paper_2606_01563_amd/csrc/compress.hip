@@ -1229,8 +1229,9 @@ __device__ __forceinline__ void tk_post_grouped(TkLds& L, const uint32_t (&key)[
 
 // The head's selection by the last workgroup to arrive (see above): the candidates and the
 // per-slice counts are read with agent-scope loads.  Bins of up to TK_CAND_LDS candidates
-// are held in LDS whole.  Of a larger bin (an octave's, very many keys, or equal ones) only the sub-bin of the k-th key is: the sums of the slices' offsets give the sub-bin and
-// its range in every slice.  Where that still has more candidates (equal keys, nearly: one
+// are held in LDS whole.  Of a larger bin (an octave's, very many keys, or equal ones) only
+// the sub-bin of the k-th key is: the sums of the slices' offsets give the sub-bin and its
+// range in every slice.  Where that still has more candidates (equal keys, nearly: one
 // sub-bin spans 2^-15 of its keys' value, or 2^-9 in an octave's bin), a pass reads them
 // from memory, a wave taking a slice at a time with 16 loads in flight per lane.
 template <bool GROUPED>
